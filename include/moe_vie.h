@@ -68,7 +68,7 @@ typedef enum { MOE_F32 = 0, MOE_BF16 = 1 } moe_dtype_t;
 
 /* Flags of moe_desc_t.flags. */
 #define MOE_FLAG_EXACT_ROUTER 1 /* compute every router logit by the exact chain
-                                   (no MFMA pre-pass); the routing result is the
+                                   (no bf16 pre-pass); the routing result is the
                                    same bit for bit, only the work differs */
 #define MOE_FLAG_SWIGLU 2       /* SwiGLU experts (bf16 layers only): see below */
 
@@ -114,10 +114,11 @@ moe_status_t moe_workspace_size(const moe_desc_t *desc, size_t *bytes);
  * the sigmoid is 1/(1 + exp(-s)) with -s clamped to [-87, 87]
  * and evaluated by Cody-Waite reduction with ln2 = 22713*2^-15 + fl32(ln2 -
  * 22713*2^-15) and a degree-7 Taylor polynomial in Horner form; the gate
- * denominator is summed in slot order. For bf16 layers the logits are first
- * computed with bf16 MFMA; every expert whose key
- * could still reach the top K under a proven bound on the difference is then
- * recomputed with the exact chain, so the result is the exact one.
+ * denominator is summed in slot order. Large bf16 batches first compute the
+ * logits with bf16 MFMA; every expert whose key could still reach the top K
+ * under a proven bound on the difference is then recomputed with the exact
+ * chain, so the result is the exact one. All other calls compute every logit
+ * by the chain, on the fp32 matrix cores.
  * Uses the workspace. */
 moe_status_t moe_route(const moe_desc_t *desc, const void *x, const void *w_router,
                        const float *bias, int32_t *topk_idx, float *topk_gate, void *workspace,

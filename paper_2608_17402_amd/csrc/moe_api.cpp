@@ -146,7 +146,8 @@ size_t elem_size(int32_t dtype) { return dtype == MOE_BF16 ? 2 : 4; }
 // of the MFMA logits GEMM (columns past E are computed from zero weight rows).
 static int32_t router_ld(const moe_desc_t& d) { return (d.E + 63) / 64 * 64; }
 
-static bool fast_router(const moe_desc_t& d) { return d.dtype == MOE_BF16 && !(d.flags & MOE_FLAG_EXACT_ROUTER); }
+// bf16 pre-pass and repair of its candidates, instead of every logit exactly.
+static bool fast_router(const moe_desc_t& d) { return !router_exact(d); }
 
 // Rows of the router logits GEMM's M-tiles (256 once the batch gives each CU
 // tiles of 256 rows, else 64).
@@ -202,9 +203,7 @@ WorkspacePlan plan_workspace(const moe_desc_t& d) {
     p.router_splits = router_splits(d);
     p.scores = take((size_t)p.router_splits * d.T * router_ld(d) * 4);
     p.wnorm = take((size_t)d.E * 4);
-    const bool small_fused = fast_router(d) && router_small_fused(d);
-    p.wr32 = take(fast_router(d) && router_small_batch(d) && !small_fused ? (size_t)d.E * d.d * 4 : 0);
-    p.wsq = take(small_fused ? (size_t)p.router_splits * router_ld(d) * 4 : 0);
+    p.wr32 = take(fast_router(d) && router_small_batch(d) ? (size_t)d.E * d.d * 4 : 0);
     p.xnorm2 = take(router_norms_in_gemm(d) ? (size_t)d.T * 4 : 0);
     p.ovf = take((size_t)(d.T + 1) * 4);
     p.cand = take((size_t)d.T * router_cand_slots(d.K) * 2);
@@ -265,8 +264,7 @@ static moe_status_t enqueue_route(const moe_desc_t& d, const WorkspacePlan& p, v
                                   hipStream_t s) {
     float* scores = region<float>(ws, p.scores);
     if (!fast_router(d)) {
-        HIP_CHECK(launch_router_scores(d, x, w_router, scores, s), "router scores");
-        HIP_CHECK(launch_topk(d, scores, bias, idx, gate, s), "top-k");
+        HIP_CHECK(launch_router_exact(d, x, w_router, bias, scores, router_ld(d), idx, gate, s), "exact router");
         return MOE_OK;
     }
     GemmArgs g{};
@@ -291,15 +289,11 @@ static moe_status_t enqueue_route(const moe_desc_t& d, const WorkspacePlan& p, v
         g.max_tiles = (d.T + 255) / 256;
         g.C2 = xnorm2;
     }
-    // Small batches: the logits GEMM (64-row tiles) also forms the weight
-    // rows' sums of squares per K part, and the repair is one launch.
-    float* wsq = router_small_fused(d) ? region<float>(ws, p.wsq) : nullptr;
-    if (wsq) g.C2 = wsq;
     HIP_CHECK(launch_gemm(d, norms ? EPI_ROUTER_F32 : EPI_STORE_F32, norms ? 256 : bm, g, s), "router logits gemm");
     int32_t* ovf = region<int32_t>(ws, p.ovf);
     HIP_CHECK(launch_router_fast_finish(d, scores, router_ld(d), p.router_splits, x, xnorm2, w_router, bias,
                                         region<float>(ws, p.wnorm),
-                                        region<float>(ws, p.wr32), wsq, region<uint16_t>(ws, p.cand),
+                                        region<float>(ws, p.wr32), region<uint16_t>(ws, p.cand),
                                         region<int32_t>(ws, p.ncand), ovf, ovf + 1, idx, gate, s),
               "router repair");
     return MOE_OK;

@@ -88,9 +88,7 @@ struct GemmArgs {
     int32_t b_rows;            // dense bf16 only: rows of B that exist (0 = N); rows past them read as zeros
     uint32_t a_bytes;          // bytes of the A operand buffer (bounds of its buffer resource)
     void* C2;                  // EPI_GELU_BWD: second output (fp32); EPI_WGRAD_F32: partial blocks;
-                               // EPI_ROUTER_F32: the rows' sums of squares [dense_rows] (fp32);
-                               // tiled dense EPI_STORE_F32: the sums of squares of B's rows over each K
-                               // part, [k_splits][N] (fp32), or null
+                               // EPI_ROUTER_F32: the rows' sums of squares [dense_rows] (fp32)
     // Backward, persistent kernel: the bf16 output (the activation, or dH) also
     // written transposed into the weight-gradient K windows, slab-major
     // [windows / 64][ct_cols][64]: sorted position p of expert e goes to window
@@ -117,7 +115,7 @@ struct GemmArgs {
 // Offsets (bytes) of every workspace region for one descriptor.
 struct WorkspacePlan {
     size_t idx, gate, scores, counts, offsets, slots, blockhist, tiles, ntiles;
-    size_t wnorm, ovf, cand, ncand, wr32, xnorm2, wsq;
+    size_t wnorm, ovf, cand, ncand, wr32, xnorm2;
     int32_t router_splits;   // split-K parts of the fast router's logits GEMM
     size_t act, eout, sact, sout;
     size_t total;
@@ -166,10 +164,10 @@ inline int32_t act_stride(const moe_desc_t& d, int32_t h) {
 int gemm_dense_bm(int32_t dtype, int64_t rows, int32_t n);
 
 // ---- launchers (each returns the first HIP error, hipSuccess otherwise)
-hipError_t launch_router_scores(const moe_desc_t& d, const void* x, const void* w_router,
-                                float* scores, hipStream_t s);
-hipError_t launch_topk(const moe_desc_t& d, const float* scores, const float* bias,
-                       int32_t* topk_idx, float* topk_gate, hipStream_t s);
+// Exact routing: every logit by the matrix-core chain into logits [T, ld]
+// (ld >= E, a multiple of 64), then sigmoids, top-K and gates.
+hipError_t launch_router_exact(const moe_desc_t& d, const void* x, const void* w_router, const float* bias,
+                               float* logits, int ld, int32_t* topk_idx, float* topk_gate, hipStream_t s);
 // Fast-router tail: norms, candidate repair with exact recomputation, and the
 // exact fallback for tokens with too many candidates. s_fast = MFMA logits,
 // rows of ld >= E floats.
@@ -180,20 +178,15 @@ hipError_t launch_topk(const moe_desc_t& d, const float* scores, const float* bi
 // wr32 [E, d], which the norm kernel writes; larger ones ignore it. xnorm2
 // [T]: the tokens' sums of squares if the logits GEMM formed them
 // (EPI_ROUTER_F32), else nullptr and the candidate kernel reads x for them.
-// wsq [nsplit][ld]: the weight rows' sums of squares over each K part (the
-// logits GEMM's second output), given exactly when router_small_fused holds;
-// the whole repair then runs in one launch and wnorm, wr32, cand, ncand and
-// the overflow queue are not touched.
 hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, int ld, int nsplit, const void* x,
                                      const float* xnorm2, const void* w_router, const float* bias, float* wnorm,
-                                     float* wr32, const float* wsq,
-                                     uint16_t* cand, int32_t* ncand, int32_t* ovf_count, int32_t* ovf_list,
+                                     float* wr32, uint16_t* cand, int32_t* ncand, int32_t* ovf_count, int32_t* ovf_list,
                                      int32_t* topk_idx, float* topk_gate, hipStream_t s);
 // Whether the fast router takes the small-batch chain kernel (fp32 weight copy).
 bool router_small_batch(const moe_desc_t& d);
-// Whether the small-batch repair runs as one launch (K <= 8, E <= 256,
-// d <= 4096): the logits GEMM then also forms the weight rows' sums of squares.
-bool router_small_fused(const moe_desc_t& d);
+// Whether every logit is computed exactly (launch_router_exact) instead of by
+// the pre-pass and the repair of its candidates.
+bool router_exact(const moe_desc_t& d);
 int router_cand_slots(int K);
 // Grouping of slots by expert; with a tile table (tiles != nullptr) the scan
 // kernel also cuts the segments into M-tiles of bm rows (as launch_build_tiles).

@@ -69,88 +69,13 @@ __device__ __forceinline__ void load8(const float* p, float* v) {
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
-// Sigmoid scores of a 64-token x 64-expert tile. Each thread owns 4 tokens
-// (ty + 16 r) x 4 experts (tx + 16 c); every accumulator is a sequential FMA
-// chain over the model width, fed from fp32 LDS tiles of 32 columns.
-constexpr int RT_TOK = 64, RT_EXP = 64, RT_DK = 32, RT_PAD = 4;
-
-template <typename TIn>
-__global__ __launch_bounds__(256) void k_router_scores(const TIn* __restrict__ x,
-                                                      const TIn* __restrict__ wr,
-                                                      float* __restrict__ scores, int T, int d,
-                                                      int E) {
-    __shared__ __attribute__((aligned(16))) float xs[RT_TOK][RT_DK + RT_PAD];
-    __shared__ __attribute__((aligned(16))) float ws[RT_EXP][RT_DK + RT_PAD];
-    const int tid = threadIdx.x;
-    const int t0 = blockIdx.x * RT_TOK;
-    const int e0 = blockIdx.y * RT_EXP;
-    const int tx = tid & 15, ty = tid >> 4;
-    float acc[4][4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = 0.0f;
-
-    const int lr = tid >> 2, lc = (tid & 3) * 8;  // this thread's 8 loaded columns
-    const int xt = t0 + lr, we = e0 + lr;
-    for (int k0 = 0; k0 < d; k0 += RT_DK) {
-        float v[8];
-        if (xt < T) {
-            load8(x + (size_t)xt * d + k0 + lc, v);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = 0.0f;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) xs[lr][lc + q] = v[q];
-        if (we < E) {
-            load8(wr + (size_t)we * d + k0 + lc, v);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = 0.0f;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) ws[lr][lc + q] = v[q];
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < RT_DK; kk += 4) {
-            float4 xv[4], wv[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) xv[r] = *reinterpret_cast<const float4*>(&xs[ty + 16 * r][kk]);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) wv[c] = *reinterpret_cast<const float4*>(&ws[tx + 16 * c][kk]);
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    // ascending column order within the chunk
-                    acc[r][c] = fmaf(xv[r].x, wv[c].x, acc[r][c]);
-                    acc[r][c] = fmaf(xv[r].y, wv[c].y, acc[r][c]);
-                    acc[r][c] = fmaf(xv[r].z, wv[c].z, acc[r][c]);
-                    acc[r][c] = fmaf(xv[r].w, wv[c].w, acc[r][c]);
-                }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int t = t0 + ty + 16 * r;
-        if (t >= T) continue;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int e = e0 + tx + 16 * c;
-            if (e < E) scores[(size_t)t * E + e] = sigmoid_fp32(acc[r][c]);
-        }
-    }
-}
-
 // Top-K selection and gates, one wavefront per token. Lane l holds experts
 // l, l + 64, ...; each of the K rounds takes the wave-wide best (key
 // descending, expert index ascending on equal keys) with a butterfly of
 // cross-lane exchanges, then the owner lane marks it taken.
 constexpr int kPerLane = kMaxE / kWave;
 
-__global__ __launch_bounds__(256) void k_topk(const float* __restrict__ scores,
+__global__ __launch_bounds__(256) void k_topk(const float* __restrict__ logits, int ld,
                                              const float* __restrict__ bias, int T, int E, int K,
                                              int32_t* __restrict__ topk_idx,
                                              float* __restrict__ topk_gate) {
@@ -163,7 +88,7 @@ __global__ __launch_bounds__(256) void k_topk(const float* __restrict__ scores,
     for (int m = 0; m < kPerLane; ++m) {
         const int e = lane + kWave * m;
         const bool ok = m < per && e < E;
-        sig[m] = ok ? scores[(size_t)t * E + e] : 0.0f;
+        sig[m] = ok ? sigmoid_fp32(logits[(size_t)t * ld + e]) : 0.0f;
         key[m] = ok ? (bias ? sig[m] + bias[e] : sig[m]) : -INFINITY;
     }
     uint32_t taken = 0;
@@ -321,6 +246,286 @@ __device__ __forceinline__ void load_row(const float* p, float (&v)[PER]) {
         v[4 * i + 1] = q.y;
         v[4 * i + 2] = q.z;
         v[4 * i + 3] = q.w;
+    }
+}
+
+// ------------------------------------------------- exact logits on the matrix cores
+//
+// v_mfma_f32_32x32x2_f32 and v_mfma_f32_16x16x4_f32 add their 2 or 4 products
+// to the accumulator one after another in ascending k, each step one fused
+// multiply-add rounded to fp32 (measured: bit-identical to a host fmaf chain
+// for ordinary, cancelling, denormal, overflowing and non-finite sums). A K
+// loop over ascending columns from a zero accumulator is therefore the logit's
+// defined chain itself, at up to 141 TFLOP/s of the card's fp32 matrix rate,
+// with no approximate pass and nothing to repair.
+//
+// Blocks of four waves, W_T x W_E wave tiles of TS tokens x TS experts (TS = 32
+// or 16). Experts are the MFMA's rows and tokens its columns, so each lane
+// holds runs of four experts of one token. Row pieces of 2 CH 16-byte chunks
+// of the block's tokens and experts stream into a ring of ST slabs with
+// direct-to-LDS copies, the chunks swizzled by row so that the 16 rows read
+// together fall on distinct banks. The barrier of a slab sits before its
+// second half's MFMAs, so the first words of the next slab are read behind
+// them. What bounds it: few waves (one image and less) wait on their own
+// chain, about 45 cycles per 16x16x4 step; many waves reach 115 of the 141
+// TFLOP/s, the fp32 MFMAs and the permutes not overlapping fully. Measured,
+// whole route, before (bf16 pre-pass GEMM and exact repair of the candidates)
+// and after: 5 tokens d 1024 E 128 20.6 -> 15 us, 7175 tokens 73 -> 33 us,
+// 18432 tokens d 768 E 64 49 -> 38 us, 65536 tokens d 1280 E 31 129 -> 65 us;
+// kernels of one image (1025 tokens, d 1536, E 256) 32.1 -> 26.7 us; fp32 2304
+// tokens d 768 E 64 61 -> 13.5 us (VALU chains before).
+// The MFMA operands of this lane (row lane % TS, k index q = lane / TS) from a
+// 16-byte row chunk in LDS: N words, one for each of the chunk's MFMAs,
+// holding column q of its 2 (TS 32) or 4 (TS 16) columns. 32 x 32 tiles read
+// bf16 chunks whole and widen by a byte permute (PERM); 16 x 16 tiles, whose
+// waves wait on their own chain, read each bf16 value straight into the high
+// half of its word (the low half stays 0) and leave no vector work between
+// the MFMAs.
+template <typename TIn, int TS>
+struct ChainFrag {
+    static constexpr int KM = TS == 32 ? 2 : 4;
+    static constexpr int N = 16 / (int)sizeof(TIn) / KM;
+    static constexpr bool BF16 = sizeof(TIn) == 2;
+    static constexpr bool PERM = BF16 && TS == 32;
+    // Byte offset of the lane's first value in the chunk.
+    __device__ static uint32_t offset(int q) { return PERM ? 0u : (uint32_t)sizeof(TIn) * q; }
+    __device__ static uint32_t selector(int q) {  // bytes of column q's half into the high half, 0 below
+        return (q & 1) ? 0x03020c0cu : 0x01000c0cu;
+    }
+    __device__ static void read(uint32_t (&w)[N], uint32_t addr) {
+        if constexpr (PERM) {
+            const u32x4_t v = lds_read16u_asm(addr);
+            w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+        } else if constexpr (BF16) {
+            asm volatile("ds_read_u16_d16_hi %0, %1" : "+v"(w[0]) : "v"(addr));
+            asm volatile("ds_read_u16_d16_hi %0, %1 offset:8" : "+v"(w[1]) : "v"(addr));
+        } else if constexpr (N == 2) {
+            u32x2_t v;
+            asm volatile("ds_read2_b32 %0, %1 offset1:2" : "=v"(v) : "v"(addr));
+            w[0] = v.x, w[1] = v.y;
+        } else {
+            asm volatile("ds_read_b32 %0, %1" : "=v"(w[0]) : "v"(addr));
+        }
+    }
+};
+
+template <typename TIn, int TS, int W_T, int W_E, int CH, int ST>
+__global__ __launch_bounds__(256) void k_router_logits(const TIn* __restrict__ x, const TIn* __restrict__ wr,
+                                                      float* __restrict__ logits, int T, int d, int E, int ld) {
+    static_assert(W_T * W_E == 4, "four waves");
+    constexpr int TR = W_T * TS, ER = W_E * TS;  // token and expert rows of the block
+    constexpr int CPR = 2 * CH, ROWB = CPR * 16;  // 16-byte chunks and bytes of a row piece
+    constexpr int SLAB = (TR + ER) * ROWB;
+    constexpr int RPP = kWave / CPR;  // rows per 1 KB copy piece
+    constexpr int P = (TR + ER) / RPP / 4;  // 1 KB copy pieces per wave and slab
+    static_assert((TR + ER) % (4 * RPP) == 0 && TR % RPP == 0 && (ST - 2) * P <= 63, "even pieces, counted in vmcnt");
+    constexpr int KB = ROWB / (int)sizeof(TIn);
+    using Frag = ChainFrag<TIn, TS>;
+    constexpr int NF = Frag::N;
+    constexpr int NA = TS == 32 ? 16 : 4;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[ST * SLAB];
+    // XCD-aware order, the expert tiles of one token tile adjacent (they
+    // share its x rows in one L2).
+    const int n_e = (E + ER - 1) / ER;
+    const int total = (T + TR - 1) / TR * n_e;
+    const int per = (total + kNumXcd - 1) / kNumXcd;
+    const int j8 = (int)blockIdx.x / kNumXcd;
+    const int lid = ((int)blockIdx.x % kNumXcd) * per + j8;
+    if (j8 >= per || lid >= total) return;
+    const int t0 = lid / n_e * TR, e0 = lid % n_e * ER;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wt = wave / W_E, we = wave % W_E;
+    const uint32_t rowb = (uint32_t)d * sizeof(TIn);
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc(x, (uint32_t)T * rowb);
+    const __amdgpu_buffer_rsrc_t wres = make_rsrc(wr, (uint32_t)E * rowb);
+    // Copy piece i of this wave: 8 rows, tokens first; token rows past T repeat
+    // the last one (not stored), expert rows past E read as zeros.
+    auto swz = [](int r) { return CPR == 8 ? (r >> 1) & 7 : r & 15; };
+    uint32_t off[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const int r = (wave + 4 * i) * RPP + lane / CPR;
+        const int c = (lane % CPR) ^ swz(r);
+        const uint32_t row = r < TR ? (uint32_t)min(t0 + r, T - 1) : (uint32_t)(e0 + r - TR);
+        off[i] = row * rowb + c * 16;
+    }
+    auto issue = [&](int slot, int kt) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const bool tok = (wave + 4 * i) * RPP < TR;  // uniform per wave
+            copy16_to_lds(tok ? xres : wres, off[i], (uint32_t)kt * (uint32_t)ROWB, smem + slot * SLAB + (wave + 4 * i) * 1024);
+        }
+    };
+    // Fragment chunk c of a row: tokens at xo, experts at eo.
+    const int fr = lane % TS, q = lane / TS;
+    const uint32_t base = lds_address(smem);
+    const uint32_t xo = base + (uint32_t)((wt * TS + fr) * ROWB) + Frag::offset(q);
+    const uint32_t eo = base + (uint32_t)((TR + we * TS + fr) * ROWB) + Frag::offset(q);
+    const int sw = swz(fr);  // rows of a fragment start at multiples of 16
+    uint32_t sel = Frag::selector(q);
+    asm volatile("" : "+v"(sel));
+    uint32_t xf[2][CH][NF] = {}, wf[2][CH][NF] = {};
+    auto read_chunk = [&](int slot, auto HC, int c) {
+        constexpr int h = decltype(HC)::value;
+        const uint32_t o = (uint32_t)slot * SLAB + (uint32_t)(((CH * h + c) ^ sw) << 4);
+        Frag::read(xf[h][c], xo + o);
+        Frag::read(wf[h][c], eo + o);
+    };
+    // Half h's words have landed; widen them (PERM). All of it before the
+    // half's first MFMA: a vector operation between two dependent MFMAs costs
+    // 8 to 20 cycles of the chain (16x16x4: 54 instead of 33 cycles per step
+    // with two permutes between).
+    auto take_half = [&](auto HC) {
+        constexpr int h = decltype(HC)::value;
+        wait_lgkmcnt0();
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int m = 0; m < NF; ++m) {
+                tie(wf[h][c][m]);
+                tie(xf[h][c][m]);
+                if constexpr (Frag::PERM) {
+                    wf[h][c][m] = __builtin_amdgcn_perm(0u, wf[h][c][m], sel);
+                    xf[h][c][m] = __builtin_amdgcn_perm(0u, xf[h][c][m], sel);
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    typedef float acc_t __attribute__((ext_vector_type(NA)));
+    acc_t acc;
+#pragma unroll
+    for (int v = 0; v < NA; ++v) acc[v] = 0.0f;
+    // Half h's MFMAs, the words of half RC of slab `slot` read between them
+    // (READ): LDS reads, unlike vector operations, do not delay the chain.
+    auto mul_half = [&](auto HC, auto RC, int slot, bool read) {
+        constexpr int h = decltype(HC)::value;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int m = 0; m < NF; ++m) {
+                const float w = __uint_as_float(wf[h][c][m]), v = __uint_as_float(xf[h][c][m]);
+                if constexpr (TS == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w, v, acc, 0, 0, 0);
+                else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v, acc, 0, 0, 0);
+                if (m == 0 && read) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_chunk(slot, RC, c);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // Slab kt's copies have landed for this wave, `ahead` younger slabs in flight.
+    auto wait_slab = [&](int ahead) {
+        static_for<ST - 1>([&](auto AC) {
+            constexpr int A = decltype(AC)::value;
+            if (ahead == A) wait_vmcnt<A * P>();
+        });
+    };
+    const int nk = d / KB;
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s)
+        if (s < nk) issue(s, s);
+    wait_slab(min(nk, ST - 1) - 1);
+    barrier_no_fence();
+    const std::integral_constant<int, 0> H0;
+    const std::integral_constant<int, 1> H1;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) read_chunk(0, H0, c);
+    int slot = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        // Slab kt + ST - 1 goes to the slot of slab kt - 1, which every wave
+        // finished reading before the last barrier.
+        if (kt + ST - 1 < nk) issue(slot == 0 ? ST - 1 : slot - 1, kt + ST - 1);
+        take_half(H0);
+        mul_half(H0, H1, slot, true);
+        take_half(H1);
+        slot = slot == ST - 1 ? 0 : slot + 1;
+        if (kt + 1 < nk) {
+            wait_slab(min(nk - 1, kt + ST - 1) - (kt + 1));
+            barrier_no_fence();
+            mul_half(H1, H0, slot, true);
+        } else {
+            mul_half(H1, H0, slot, false);
+        }
+    }
+    // D rows (experts) of lane l: TS == 32: 8 g + 4 (l / 32) + v; 16: 4 (l / 16) + v.
+    const int t = t0 + wt * TS + fr;
+    if (t >= T) return;
+    float* const row = logits + (size_t)t * ld + e0 + we * TS + 4 * q;
+#pragma unroll
+    for (int g = 0; g < NA / 4; ++g)
+        *reinterpret_cast<float4*>(row + 8 * g) = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+}
+
+// Maximum of an unsigned key over each aligned group of 16 lanes, in every lane.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_umax(uint32_t a) {
+    return max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ uint32_t row16_umax(uint32_t v) {
+    v = dpp_umax<0xB1>(v);
+    v = dpp_umax<0x4E>(v);
+    v = dpp_umax<0x141>(v);
+    return dpp_umax<0x140>(v);
+}
+
+// Sigmoids, top-K and gates from exact logits for up to 16 PER experts: 16
+// lanes per token (lane g holds experts g PER ..), 4 tokens per wave. Keys
+// compare as integers of the same order (an unused or taken slot is 0, below
+// every key); each of the K rounds takes the group's largest key, lowest lane
+// and then lowest expert on ties. The winners' experts and the token's
+// sigmoids meet in LDS for the denominator in slot order.
+template <int PER>
+__global__ __launch_bounds__(256) void k_topk16(const float* __restrict__ logits, int ld,
+                                               const float* __restrict__ bias, int T, int E, int K,
+                                               int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
+    static_assert(PER % 4 == 0, "whole 16-byte loads");
+    __shared__ __attribute__((aligned(16))) float ssig[16][16 * PER + 4];
+    __shared__ int32_t sidx[16][kMaxK];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int g = lane & 15;
+    const int tl = threadIdx.x / 16;
+    const int t = blockIdx.x * (blockDim.x / 16) + tl;
+    const int e0 = g * PER;
+    float s[PER], b[PER];
+    load_row<PER>(logits + (size_t)min(t, T - 1) * ld + (e0 < ld ? e0 : 0), s);
+#pragma unroll
+    for (int m = 0; m < PER; ++m) b[m] = bias ? bias[min(e0 + m, E - 1)] : 0.0f;
+    uint32_t key[PER];
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+        s[m] = sigmoid_fp32(s[m]);
+        const uint32_t u = __float_as_uint(bias ? s[m] + b[m] : s[m]);
+        key[m] = e0 + m < E ? ((u & 0x80000000u) ? ~u : (u | 0x80000000u)) : 0u;
+    }
+#pragma unroll
+    for (int m = 0; m < PER; m += 4)
+        *reinterpret_cast<float4*>(&ssig[tl][e0 + m]) = make_float4(s[m], s[m + 1], s[m + 2], s[m + 3]);
+    for (int j = 0; j < K; ++j) {
+        uint32_t mine = key[0];
+#pragma unroll
+        for (int m = 1; m < PER; ++m) mine = max(mine, key[m]);
+        const uint32_t best = row16_umax(mine);
+        const uint32_t holders = (uint32_t)(__ballot(mine == best) >> (lane & 48)) & 0xffffu;
+        if (g == __ffs(holders) - 1) {
+            int mi = PER - 1;
+#pragma unroll
+            for (int m = PER - 2; m >= 0; --m) mi = key[m] == best ? m : mi;
+#pragma unroll
+            for (int m = 0; m < PER; ++m) key[m] = m == mi ? 0u : key[m];
+            sidx[tl][j] = e0 + mi;
+        }
+    }
+    __syncthreads();
+    if (t >= T) return;
+    // Gate denominator in slot order.
+    const int my = g < K ? sidx[tl][g] : 0;
+    float den = ssig[tl][sidx[tl][0]];
+    for (int j = 1; j < K; ++j) den = den + ssig[tl][sidx[tl][j]];
+    if (g < K) {
+        topk_idx[(size_t)t * K + g] = my;
+        topk_gate[(size_t)t * K + g] = ssig[tl][my] / den;
     }
 }
 
@@ -987,392 +1192,55 @@ __global__ __launch_bounds__(kWave) void k_router_chain_direct(const bf16_t* __r
     chain_select<TPB, LPT, 1>(lds_dyn, tl, g, t, T, nc, K, on, ec, acc, bc, bias != nullptr, topk_idx, topk_gate);
 }
 
-// Small batches with K <= 8, at most 256 experts and d <= 4096: the whole
-// repair in one launch. A one-wave block takes 4 tokens, 16 lanes each (lane
-// g holding experts g PER .. g PER + PER - 1, as in the candidate kernel):
-//  - the weight-row norms come from the logits GEMM's per-part sums of
-//    squares (wsq [nsplit][ld]), the token norms from the token's x row,
-//    which the block stages in LDS widened to fp32 for the chains anyway;
-//  - the interval test of the candidate kernel, the candidate list in LDS;
-//  - lane g runs the exact chain of the token's candidate g (slot 16 tl + g).
-//    The weight rows of the block's 64 slots stream through LDS in chunks of
-//    128 columns, three buffers deep, by direct-to-LDS copies of 1 KB that
-//    each carry 256 contiguous bytes of four slots' rows (8 cache lines per
-//    copy, where a row per lane would touch 64). The chain is a run of
-//    dependent multiply-adds; the bf16 weights of the next 16 columns are
-//    widened between them, so that the adds never wait on the widening;
-//  - then the chain kernels' selection;
-//  - a token with more candidates than its 16 slots is routed by the block
-//    itself: every E logit by the same chain, recipe S and the exact top-K,
-//    so no queue crosses blocks.
-// Every multiply-add chain and selection is the same as on the other paths,
-// so indices and gates are identical bit for bit.
-constexpr int kSmallTpb = 4;      // tokens per one-wave block
-constexpr int kSmallChunk = 128;  // weight columns per LDS chunk
-constexpr int kSmallBufs = 3;     // chunk buffers (two chunks in flight)
-// One copy: 16-byte piece j (columns 8j .. 8j + 7 of the chunk) of slot
-// 4i + q at byte 16 (4 j + q); 64 bytes of padding after each copy put the 16
-// slots that a quarter wave reads at once on distinct LDS banks.
-constexpr int kSmallCopyBytes = kWave * 16 + 64;
-constexpr int kSmallBufBytes = (kWave / 4) * kSmallCopyBytes;
-constexpr int kSmallSelBytes = kSmallTpb * (16 * 12 + kMaxK * 8);
-static_assert(kSmallSelBytes + 256 * 4 <= kSmallBufs * kSmallBufBytes, "selection arrays fit the buffers");
+}  // namespace
 
-// 16 bytes from LDS at addr + OFF (inline assembly: the compiler neither sees
-// the read nor waits for it; the caller waits with lgkmcnt and pins the
-// result with tie()).
-template <int OFF>
-__device__ __forceinline__ u32x4_t lds_read16u_off(uint32_t addr) {
-    u32x4_t r;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
+namespace {
 
-// Element j (0..15) of 16 bf16 held in two 16-byte registers, widened.
-__device__ __forceinline__ float bf16_elem(const u32x4_t (&w)[2], int j) {
-    const uint32_t bits = w[j / 8][(j / 2) % 4];
-    return __uint_as_float((j & 1) ? (bits & 0xffff0000u) : (bits << 16));
-}
-
-// Dynamic LDS of k_router_small: the 4 x rows (d + 4 floats each: the pad
-// spreads the 4 tokens' reads over the banks) and the chunk buffers, which
-// the selection's arrays and the overflow path's sigmoids reuse afterwards.
-// At d = 1536 this and the static arrays stay under half the LDS, so two
-// blocks share a CU (one image's 257 blocks all run at once).
-size_t router_small_lds_bytes(int d) {
-    return (size_t)kSmallTpb * (d + 4) * 4 + (size_t)kSmallBufs * kSmallBufBytes;
-}
-
-template <int PER>
-__global__ __launch_bounds__(kWave) void k_router_small(const float* __restrict__ s_fast, int nsplit,
-                                                      size_t sstride, int ld, const float* __restrict__ wsq,
-                                                      const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr,
-                                                      const float* __restrict__ bias, int T, int d, int E, int K,
-                                                      float cst, int32_t* __restrict__ topk_idx,
-                                                      float* __restrict__ topk_gate) {
-    constexpr int LPA = 16, NS = 16, TPB = kSmallTpb, EM = LPA * PER;
-    static_assert(TPB * LPA == kWave, "one wave of 4 tokens");
-    static_assert(PER % 4 == 0 && 64 % PER == 0, "whole 16-byte loads inside a row of a multiple of 64");
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds_dyn[];
-    __shared__ __attribute__((aligned(16))) float sb[EM];
-    __shared__ __attribute__((aligned(16))) float swn[EM];
-    __shared__ uint16_t scand[TPB][NS];
-    __shared__ int snc[TPB];  // candidates per token (more than NS: the block routes it in full)
-    const int lane = threadIdx.x;
-    const int g = lane % LPA, tl = lane / LPA;
-    const int t = blockIdx.x * TPB + tl;
-    const bool live = t < T;  // uniform within the token's lanes
-    const uint64_t grp = ((1ull << LPA) - 1ull) << (lane - g);
-    const int XS = d + 4;  // x row stride in LDS (floats)
-    float* xs = reinterpret_cast<float*>(lds_dyn);
-    uint8_t* wbuf = lds_dyn + (size_t)TPB * XS * 4;
-    uint8_t* sel = wbuf;                                        // after the chains
-    float* ssig = reinterpret_cast<float*>(wbuf + kSmallSelBytes);  // overflow path
-
-    // Every global load of the token phase is issued before the first use:
-    // the partial logits of the lane's experts, the parts' sums of squares of
-    // the weight rows and the x pieces (tokens past T read row T - 1, lanes
-    // past the logit row read column 0; neither is used).
-    const int e0 = g * PER;
-    float pv[8][PER];
-    {
-        const float* row = s_fast + (size_t)(live ? t : T - 1) * ld + (e0 < ld ? e0 : 0);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) load_row<PER>(row + (q < nsplit ? q * sstride : 0), pv[q]);
+template <typename TIn>
+hipError_t launch_logits(const moe_desc_t& d, const void* x, const void* w_router, float* logits, int ld,
+                         hipStream_t s) {
+    auto go = [&](auto kern, int tr, int er) -> hipError_t {
+        const long long total = ((long long)d.T + tr - 1) / tr * ((d.E + er - 1) / er);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((total + kNumXcd - 1) / kNumXcd * kNumXcd)), dim3(256), 0, s,
+                           static_cast<const TIn*>(x), static_cast<const TIn*>(w_router), logits, d.T, d.d, d.E, ld);
+        return hipGetLastError();
+    };
+    // 32 x 32 wave tiles read a quarter of the LDS bytes and permute half as
+    // much per multiply-add, but a chain step takes 32 cycles instead of 8 to
+    // 12 and there are a quarter of the waves: they pay once the 16 x 16 tiles
+    // give each SIMD three or more waves (T E / 1024; 459k: 18.5 us against
+    // 24.6, 918k: 36 against 33, 1.05M: 29 against 27, 16.8M: 566 against 452).
+    const int64_t work = (int64_t)d.T * ((d.E + 31) / 32 * 32);
+    if (work < 800000) {
+        // Two slabs of 256-byte row pieces, or four of 128 bytes (d an odd
+        // multiple of 64 in bf16).
+        if ((size_t)d.d * sizeof(TIn) % 256 == 0) return go(k_router_logits<TIn, 16, 2, 2, 8, 2>, 32, 32);
+        return go(k_router_logits<TIn, 16, 2, 2, 4, 4>, 32, 32);
     }
-    constexpr int EPL = EM / kWave > 0 ? EM / kWave : 1;
-    float part[EPL][8];
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int e = lane + kWave * m;
-        const int ec = e < E ? e : 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) part[m][q] = wsq[(size_t)(q < nsplit ? q : 0) * ld + ec];
-    }
-    // x: sixteen 16-byte pieces per lane and round (2048 columns), the last
-    // round's pieces past d re-reading the row's last piece.
-    const bf16_t* xt = x + (size_t)(live ? t : T - 1) * d;
-    constexpr int XU = 16;
-    u32x4_t xr16[XU];
-#pragma unroll
-    for (int u = 0; u < XU; ++u) {
-        const int i = g * 8 + u * LPA * 8;
-        xr16[u] = *reinterpret_cast<const u32x4_t*>(xt + (i < d ? i : d - 8));
-    }
-
-    // Selection biases and weight-row norms: the parts' sums of squares added
-    // in part order and raised by 0.1 % as the norm kernel does (an upper
-    // bound is all the interval needs).
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int e = lane + kWave * m;
-        float ss = part[m][0];
-#pragma unroll
-        for (int q = 1; q < 8; ++q) ss = q < nsplit ? ss + part[m][q] : ss;
-        if (e < E) {
-            swn[e] = sqrtf(ss) * 1.001f + 1e-30f;
-            sb[e] = bias ? bias[e] : 0.0f;
-        }
-    }
-
-    // x rows widened to fp32 in LDS, and the token's sum of squares from the
-    // same values.
-    float ssq[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // four partial sums: no long dependent run
-    for (int i0 = g * 8; i0 < d; i0 += XU * LPA * 8) {
-        if (i0 != g * 8) {  // rounds past the first (d > 2048)
-#pragma unroll
-            for (int u = 0; u < XU; ++u) {
-                const int i = i0 + u * LPA * 8;
-                xr16[u] = *reinterpret_cast<const u32x4_t*>(xt + (i < d ? i : d - 8));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < XU; ++u) {
-            const int i = i0 + u * LPA * 8;
-            if (i < d) {
-                const u32x4_t v = xr16[u];
-                const float f[8] = {__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                                    __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u),
-                                    __uint_as_float(v.z << 16), __uint_as_float(v.z & 0xffff0000u),
-                                    __uint_as_float(v.w << 16), __uint_as_float(v.w & 0xffff0000u)};
-                *reinterpret_cast<float4*>(xs + tl * XS + i) = make_float4(f[0], f[1], f[2], f[3]);
-                *reinterpret_cast<float4*>(xs + tl * XS + i + 4) = make_float4(f[4], f[5], f[6], f[7]);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) ssq[q % 4] = fmaf(f[q], f[q], ssq[q % 4]);
-            }
-        }
-    }
-    float ssx = (ssq[0] + ssq[1]) + (ssq[2] + ssq[3]);
-#pragma unroll
-    for (int off = LPA / 2; off > 0; off >>= 1) ssx += __shfl_xor(ssx, off);
-    const float xn = live ? sqrtf(ssx) * 1.001f + 1e-30f : 0.0f;
-
-    // Fast logits of the lane's experts: the K parts added in part order.
-    float sf[PER];
-#pragma unroll
-    for (int m = 0; m < PER; ++m) sf[m] = pv[0][m];
-#pragma unroll
-    for (int q = 1; q < 8; ++q)
-#pragma unroll
-        for (int m = 0; m < PER; ++m) sf[m] = q < nsplit ? sf[m] + pv[q][m] : sf[m];
-    __syncthreads();
-    // The interval test, as in the candidate kernel.
-    // The lane's biases and norms in 16-byte LDS reads (entries past E are
-    // read but not used), then every interval without a branch.
-    float bv[PER], wn[PER];
-#pragma unroll
-    for (int q = 0; q < PER / 4; ++q) {
-        const float4 b4 = *reinterpret_cast<const float4*>(sb + e0 + 4 * q);
-        const float4 n4 = *reinterpret_cast<const float4*>(swn + e0 + 4 * q);
-        bv[4 * q] = b4.x, bv[4 * q + 1] = b4.y, bv[4 * q + 2] = b4.z, bv[4 * q + 3] = b4.w;
-        wn[4 * q] = n4.x, wn[4 * q + 1] = n4.y, wn[4 * q + 2] = n4.z, wn[4 * q + 3] = n4.w;
-    }
-    float lo[PER], hi[PER];
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const bool ok = live && e0 + m < E;
-        const float key = sigmoid_fast(sf[m]) + bv[m];
-        const float delta = 0.25f * (cst * xn * wn[m]) + 4e-6f + 1e-6f * fabsf(bv[m]);
-        lo[m] = ok ? key - delta : -INFINITY;
-        hi[m] = ok ? key + delta : -INFINITY;
-    }
-    float t1 = -INFINITY, t2 = -INFINITY, t3 = -INFINITY;
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const float v = lo[m];
-        t3 = fmaxf(t3, fminf(t2, v));
-        t2 = fmaxf(t2, fminf(t1, v));
-        t1 = fmaxf(t1, v);
-    }
-    float L = -INFINITY;
-    int used = 0;
-    for (int j = 0; j < K; ++j) {
-        const float mine = used == 0 ? t1 : (used == 1 ? t2 : (used == 2 ? t3 : -INFINITY));
-        const float gmax = group_max<LPA>(mine);
-        const uint64_t holders = __ballot(used < 3 && mine == gmax) & grp;
-        if (holders && lane == __ffsll((unsigned long long)holders) - 1) ++used;
-        L = gmax;
-    }
-    // Candidates: lane g's in expert order after those of lanes 0 .. g - 1
-    // (an inclusive scan of the lanes' counts along the 16-lane DPP row).
-    uint32_t cbits = 0;
-#pragma unroll
-    for (int m = 0; m < PER; ++m) cbits |= (live && hi[m] >= L) ? (1u << m) : 0u;
-    const int cnt = __popc(cbits);
-    int incl = cnt;
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, false);  // row_shr:1
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, false);  // row_shr:2
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, false);  // row_shr:4
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, false);  // row_shr:8
-    const int nc = __builtin_amdgcn_update_dpp(0, incl, 0x15F, 0xF, 0xF, false);  // row_newbcast:15
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int pos = incl - cnt + __popc(cbits & ((1u << m) - 1u));
-        if (((cbits >> m) & 1u) && pos < NS) scand[tl][pos] = (uint16_t)(e0 + m);
-    }
-    if (g == 0) snc[tl] = nc;
-    __syncthreads();
-
-    // Exact chain of candidate g (slot 16 tl + g).
-    const int ncx = nc > NS ? 0 : nc;  // an overflowing token is routed below
-    const bool on[1] = {g < ncx};
-    const int ec[1] = {on[0] ? (int)scand[tl][g] : 0};
-    const float bc[1] = {(bias && on[0]) ? sb[ec[0]] : 0.0f};
-    float acc[1] = {0.0f};
-    if (__ballot(on[0]) != 0) {
-        // Copy sources: in copy i this lane carries 16 bytes of slot
-        // 4i + lane % 4, piece lane / 4 of the chunk's 256 bytes of that
-        // slot's row. Free slots copy row 0 (in bounds, never read); the rest
-        // of a ragged last chunk is never read either.
-        int ncs[TPB];
-#pragma unroll
-        for (int u = 0; u < TPB; ++u) ncs[u] = snc[u] > NS ? 0 : snc[u];
-        uint32_t roff[kWave / 4];
-#pragma unroll
-        for (int i = 0; i < kWave / 4; ++i) {
-            const int slot = 4 * i + (lane & 3);
-            const int su = slot / NS, sg = slot % NS;
-            const int e = sg < ncs[su] ? (int)scand[su][sg] : 0;
-            roff[i] = (uint32_t)e * (uint32_t)d * 2u + (uint32_t)(lane >> 2) * 16u;
-        }
-        const __amdgpu_buffer_rsrc_t rw = make_rsrc(wr, (uint32_t)((size_t)E * d * 2));
-        auto copy_chunk = [&](int c) {
-            uint8_t* dst = wbuf + (size_t)(c % kSmallBufs) * kSmallBufBytes;
-#pragma unroll
-            for (int i = 0; i < kWave / 4; ++i)
-                copy16_to_lds(rw, roff[i], (uint32_t)c * (kSmallChunk * 2), dst + i * kSmallCopyBytes);
-        };
-        // This lane's slot in buffer 0 (piece j at + 64 j) and its token's x row.
-        const uint32_t wa0 = lds_address(wbuf) + (uint32_t)(lane >> 2) * kSmallCopyBytes + (uint32_t)(lane & 3) * 16u;
-        const uint32_t xa0 = lds_address(reinterpret_cast<uint8_t*>(xs + tl * XS));
-        const int nch = (d + kSmallChunk - 1) / kSmallChunk;
-        float a = 0.0f;
-        // Register sets of three units in rotation (raw 16-byte reads) and the
-        // widened weights of two units.
-        u32x4_t wv[3][2] = {}, xv[3][4] = {};
-        float wf[2][16];
-        copy_chunk(0);
-        if (nch > 1) copy_chunk(1);
-        for (int c = 0; c < nch; ++c) {
-            // Chunk c is in LDS once at most one chunk's copies are in flight
-            // (a single wave: its own copies).
-            if (c + 1 < nch) wait_vmcnt<kWave / 4>(); else wait_vmcnt<0>();
-            // Chunk c - 1's buffer is free: every LDS read of it was awaited.
-            if (c + 2 < nch) copy_chunk(c + 2);
-            const uint32_t wa = wa0 + (uint32_t)(c % kSmallBufs) * kSmallBufBytes;
-            const uint32_t xa = xa0 + (uint32_t)c * (kSmallChunk * 4);
-            const int left = (d - c * kSmallChunk) / 16;
-            const int nu = left < kSmallChunk / 16 ? left : kSmallChunk / 16;  // units of 16 columns
-            auto issue = [&](auto KC) {
-                constexpr int k = decltype(KC)::value;
-                constexpr int r = k % 3;
-                wv[r][0] = lds_read16u_off<k * 128>(wa);
-                wv[r][1] = lds_read16u_off<k * 128 + 64>(wa);
-                xv[r][0] = lds_read16u_off<k * 64>(xa);
-                xv[r][1] = lds_read16u_off<k * 64 + 16>(xa);
-                xv[r][2] = lds_read16u_off<k * 64 + 32>(xa);
-                xv[r][3] = lds_read16u_off<k * 64 + 48>(xa);
-            };
-            auto settle = [&](int r) {
-                tie(wv[r][0]);
-                tie(wv[r][1]);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) tie(xv[r][q]);
-            };
-            issue(std::integral_constant<int, 0>{});
-            if (nu > 1) issue(std::integral_constant<int, 1>{});
-            if (nu > 1) wait_lgkmcnt<6>(); else wait_lgkmcnt<0>();
-            settle(0);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) wf[0][j] = bf16_elem(wv[0], j);
-            static_for<kSmallChunk / 16>([&](auto KC) {
-                constexpr int k = decltype(KC)::value;
-                constexpr int r = k % 3, r1 = (k + 1) % 3;
-                if (k < nu) {
-                    wait_lgkmcnt<0>();  // unit k + 1's reads (the last ones issued)
-                    settle(r1);
-                    if constexpr (k + 2 < kSmallChunk / 16)
-                        if (k + 2 < nu) issue(std::integral_constant<int, k + 2>{});
-                    // Unit k's 16 multiply-adds in column order, unit k + 1's
-                    // weights widened in between.
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) {
-                        a = fmaf(__uint_as_float(xv[r][j / 4][j % 4]), wf[k % 2][j], a);
-                        wf[(k + 1) % 2][j] = bf16_elem(wv[r1], j);
-                    }
-                }
-            });
-        }
-        acc[0] = a;
-    }
-    // The selection's arrays reuse the chunk buffers (no copy is in flight).
-    chain_select<TPB, LPA, 1>(sel, tl, g, t, T, ncx, K, on, ec, acc, bc, bias != nullptr, topk_idx, topk_gate);
-
-    // Overflowing tokens, one at a time: lane l runs the chains of experts
-    // l, l + 64, ... side by side (at most 4 for E <= 256), each the same fma
-    // sequence over i = 0..d-1 from +0, then recipe S and the exact top-K.
-    for (int u = 0; u < TPB; ++u) {
-        if (snc[u] <= NS) continue;  // uniform: one LDS value for the whole wave
-        const int tu = blockIdx.x * TPB + u;
-        const float* xr = xs + u * XS;
-        constexpr int EPL = EM / kWave > 0 ? EM / kWave : 1;
-        float av[EPL];
-        const bf16_t* we[EPL];
-#pragma unroll
-        for (int m = 0; m < EPL; ++m) {
-            av[m] = 0.0f;
-            const int e = lane + kWave * m;
-            we[m] = wr + (size_t)(e < E ? e : 0) * d;
-        }
-        for (int i = 0; i < d; i += 8) {
-            const float4 x0 = *reinterpret_cast<const float4*>(xr + i);
-            const float4 x1 = *reinterpret_cast<const float4*>(xr + i + 4);
-            const float xv8[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            u32x4_t wq4[EPL];
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) wq4[m] = *reinterpret_cast<const u32x4_t*>(we[m] + i);
-#pragma unroll
-            for (int m = 0; m < EPL; ++m) {
-                const uint32_t wq[4] = {wq4[m].x, wq4[m].y, wq4[m].z, wq4[m].w};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    av[m] = fmaf(xv8[2 * q], __uint_as_float(wq[q] << 16), av[m]);
-                    av[m] = fmaf(xv8[2 * q + 1], __uint_as_float(wq[q] & 0xffff0000u), av[m]);
-                }
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < EPL; ++m) {
-            const int e = lane + kWave * m;
-            if (e < E) ssig[e] = sigmoid_fp32(av[m]);
-        }
-        __syncthreads();
-        exact_select_wave(ssig, bias, E, K, tu, lane, topk_idx, topk_gate);
-        __syncthreads();
-    }
+    if (d.E <= 32) return go(k_router_logits<TIn, 32, 4, 1, 4, 2>, 128, 32);
+    return go(k_router_logits<TIn, 32, 2, 2, 4, 2>, 64, 64);
 }
 
 }  // namespace
 
-hipError_t launch_router_scores(const moe_desc_t& d, const void* x, const void* w_router,
-                                float* scores, hipStream_t s) {
-    dim3 grid((d.T + RT_TOK - 1) / RT_TOK, (d.E + RT_EXP - 1) / RT_EXP);
-    if (d.dtype == MOE_BF16)
-        hipLaunchKernelGGL(k_router_scores<bf16_t>, grid, dim3(256), 0, s,
-                           static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w_router), scores,
-                           d.T, d.d, d.E);
-    else
-        hipLaunchKernelGGL(k_router_scores<float>, grid, dim3(256), 0, s, static_cast<const float*>(x),
-                           static_cast<const float*>(w_router), scores, d.T, d.d, d.E);
-    return hipGetLastError();
-}
-
-hipError_t launch_topk(const moe_desc_t& d, const float* scores, const float* bias,
-                       int32_t* topk_idx, float* topk_gate, hipStream_t s) {
-    const int per_block = 256 / kWave;
-    dim3 grid((d.T + per_block - 1) / per_block);
-    hipLaunchKernelGGL(k_topk, grid, dim3(256), 0, s, scores, bias, d.T, d.E, d.K, topk_idx, topk_gate);
-    return hipGetLastError();
+hipError_t launch_router_exact(const moe_desc_t& d, const void* x, const void* w_router, const float* bias,
+                               float* logits, int ld, int32_t* topk_idx, float* topk_gate, hipStream_t s) {
+    const hipError_t e = d.dtype == MOE_BF16 ? launch_logits<bf16_t>(d, x, w_router, logits, ld, s)
+                                             : launch_logits<float>(d, x, w_router, logits, ld, s);
+    if (e != hipSuccess) return e;
+    if (d.E > 256) {
+        hipLaunchKernelGGL(k_topk, dim3((d.T + 3) / 4), dim3(256), 0, s, logits, ld, bias, d.T, d.E, d.K, topk_idx,
+                           topk_gate);
+        return hipGetLastError();
+    }
+    auto go = [&](auto kern) -> hipError_t {
+        hipLaunchKernelGGL(kern, dim3((d.T + 15) / 16), dim3(256), 0, s, logits, ld, bias, d.T, d.E, d.K, topk_idx,
+                           topk_gate);
+        return hipGetLastError();
+    };
+    if (d.E <= 64) return go(k_topk16<4>);
+    if (d.E <= 128) return go(k_topk16<8>);
+    return go(k_topk16<16>);
 }
 
 }  // namespace moe
@@ -1389,36 +1257,30 @@ float router_fast_bound_constant(int d) {
 
 bool router_small_batch(const moe_desc_t& d) { return d.T < 256 * 64; }
 
-bool router_small_fused(const moe_desc_t& d) {
-    return router_small_batch(d) && d.K <= 8 && d.E <= 256 && d.d <= 4096;
+// Every logit by the matrix-core chain, or only the candidates of a bf16
+// pre-pass? The chain costs 2 T E d flop at 100 to 115 TFLOP/s; the pre-pass
+// runs at the bf16 rate and its repair costs about eight chains per token plus
+// five launches. Measured (us, exact against repair): E = 64 wins at every T
+// (768 wide: 13 / 17 at 5 tokens, 42 / 59 at 32768, 73 / 89 at 65536); with
+// 64 < E <= 256 up to the large-batch chain kernel (E = 128, d = 1024: 52 / 138
+// at 16383 tokens, but 68 / 68 at 18432 and 163 / 113 at 65536; E = 256, d =
+// 1536: 125 / 187 at 16383, 151 / 116 at 18432); with more experts only where
+// the interval test fails: its width grows with d |x| |w|, and past d = 2048
+// most experts become candidates and most tokens go through the overflow
+// queue (d = 4096, E = 256, weights of deviation 0.02: 94 / 520 us at 1025
+// tokens, 1.1 / 37 ms at 65536; E = 300, d = 1024: 34 / 31 at 1025 tokens).
+bool router_exact(const moe_desc_t& d) {
+    return d.dtype != MOE_BF16 || (d.flags & MOE_FLAG_EXACT_ROUTER) || d.d > 2048 || d.E <= 64 ||
+           (d.E <= 256 && router_small_batch(d));
 }
 
 hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, int ld, int nsplit, const void* x,
                                      const float* xnorm2, const void* w_router, const float* bias, float* wnorm,
-                                     float* wr32, const float* wsq,
-                                     uint16_t* cand, int32_t* ncand, int32_t* ovf_count, int32_t* ovf_list,
+                                     float* wr32, uint16_t* cand, int32_t* ncand, int32_t* ovf_count, int32_t* ovf_list,
                                      int32_t* topk_idx, float* topk_gate, hipStream_t s) {
     const bf16_t* xb = static_cast<const bf16_t*>(x);
     const bf16_t* wb = static_cast<const bf16_t*>(w_router);
     if (nsplit < 1 || nsplit > 8) return hipErrorInvalidValue;  // the candidate kernels add at most 8 parts
-    if (wsq) {  // one launch: norms, candidates, chains, selection and overflow
-        if (!router_small_fused(d)) return hipErrorInvalidValue;
-        const size_t shm = router_small_lds_bytes(d.d);
-        auto launch = [&](auto kern) -> hipError_t {
-            if (shm > 65536) {
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-                if (e != hipSuccess) return e;
-            }
-            hipLaunchKernelGGL(kern, dim3((d.T + 3) / 4), dim3(kWave), shm, s, s_fast, nsplit, (size_t)d.T * ld, ld,
-                               wsq, xb, wb, bias, d.T, d.d, d.E, d.K, router_fast_bound_constant(d.d), topk_idx,
-                               topk_gate);
-            return hipGetLastError();
-        };
-        if (d.E <= 64) return launch(k_router_small<4>);
-        if (d.E <= 128) return launch(k_router_small<8>);
-        return launch(k_router_small<16>);
-    }
     const bool small = router_small_batch(d);
     // Weight-row norms (the token norms are formed in the candidate kernel);
     // for small batches also the fp32 copy of the weights the chains read.
@@ -1437,8 +1299,7 @@ hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, i
                        ovf_list, nsplit, sstride)
     // E / LPA experts per lane (at least 4), so that every lane of a token
     // holds experts and L is taken over all of them.
-    if (d.E <= 64) { if (ns == 16) MOE_CAND(16, 4, 16); else MOE_CAND(16, 4, 32); }
-    else if (d.E <= 128) { if (ns == 16) MOE_CAND(16, 8, 16); else MOE_CAND(16, 8, 32); }
+    if (d.E <= 128) { if (ns == 16) MOE_CAND(16, 8, 16); else MOE_CAND(16, 8, 32); }
     else if (d.E <= 256) { if (ns == 16) MOE_CAND(16, 16, 16); else MOE_CAND(16, 16, 32); }
     else if (d.E <= 512) { if (ns == 16) MOE_CAND(64, 8, 16); else MOE_CAND(64, 8, 32); }
     else { if (ns == 16) MOE_CAND(64, 16, 16); else MOE_CAND(64, 16, 32); }
@@ -1452,8 +1313,7 @@ hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, i
                        (d.T + TPBv - 1) / TPBv, ovf_count, ovf_list)
 #define MOE_CHAIN_E(TPBv, LPTv, CPLv, DCv)                                                                     \
     do {                                                                                                    \
-        if (d.E <= 64) MOE_CHAIN(TPBv, LPTv, CPLv, 64, DCv);                                                \
-        else if (d.E <= 256) MOE_CHAIN(TPBv, LPTv, CPLv, 256, DCv);                                         \
+        if (d.E <= 256) MOE_CHAIN(TPBv, LPTv, CPLv, 256, DCv);                                         \
         else MOE_CHAIN(TPBv, LPTv, CPLv, 1024, 16);                                                         \
     } while (0)
     const int big_tpb = ns == 16 ? 256 : 128;
