@@ -167,6 +167,10 @@ __device__ __forceinline__ void lds_read_tr8_asm(u32x2_t& r, uint32_t addr) {
     asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r) : "v"(addr));
 }
 __device__ __forceinline__ void tie(u32x2_t& v) { asm volatile("" : "+v"(v)); }
+// Two words 8 bytes apart (the two fp32 MFMAs' operands in a 16-byte chunk).
+__device__ __forceinline__ void lds_read2_asm(u32x2_t& r, uint32_t addr) {
+    asm volatile("ds_read2_b32 %0, %1 offset1:2" : "=v"(r) : "v"(addr));
+}
 // One accumulator moved to a vector register at this point of the program
 // (volatile: not hoisted, so only one staged block's values are live at once).
 __device__ __forceinline__ float acc_read(float x) {

@@ -301,7 +301,7 @@ struct ChainFrag {
             asm volatile("ds_read_u16_d16_hi %0, %1 offset:8" : "+v"(w[1]) : "v"(addr));
         } else if constexpr (N == 2) {
             u32x2_t v;
-            asm volatile("ds_read2_b32 %0, %1 offset1:2" : "=v"(v) : "v"(addr));
+            lds_read2_asm(v, addr);
             w[0] = v.x, w[1] = v.y;
         } else {
             asm volatile("ds_read_b32 %0, %1" : "=v"(w[0]) : "v"(addr));
