@@ -60,7 +60,8 @@ TRAFFIC_SOURCES = ("paper_2608_17402_amd/csrc/gemm.hip", "paper_2608_17402_amd/c
 # the forward pair and backward.hip).
 BACKWARD_TRAFFIC_SOURCE_HASH = "10192b99fe832cc7"
 BACKWARD_TRAFFIC_BYTES = {"vitg_skew_bf16": 41177098056, "vith_swiglu_bf16": 47912615423}
-BACKWARD_TRAFFIC_SOURCES = TRAFFIC_SOURCES + ("paper_2608_17402_amd/csrc/backward.hip",)
+BACKWARD_TRAFFIC_SOURCES = TRAFFIC_SOURCES + ("paper_2608_17402_amd/csrc/backward.hip",
+                                                      "paper_2608_17402_amd/csrc/wgrad.hip")
 
 
 def source_hash(files):

@@ -1,9 +1,8 @@
 // Data-movement kernels of the expert-MLP backward: weight transposes, the
 // plan of the weight-gradient products (per-expert K windows cut into work
-// items) and the sum of their partial blocks, the transposing gather into the
-// windows and the zeroing of empty experts' windows, and the per-token sum of
-// the slot gradients. The
-// products themselves run on the MFMA kernels of gemm.hip.
+// items), its row tables and the sum of their partial blocks, and the per-token
+// sum of the slot gradients. The products themselves run on the MFMA kernels
+// of gemm.hip and wgrad.hip.
 #include "moe_internal.h"
 
 namespace moe {
@@ -59,10 +58,10 @@ __global__ __launch_bounds__(256) void k_transpose_w(const bf16_t* __restrict__ 
 }
 
 // Plan of the weight-gradient products, one workgroup:
-//  - K windows: expert e owns columns koff[e] .. koff[e+1] of the transposed
-//    operands, its row count rounded up to a multiple of 64 (the K slab) and
-//    to at least two slabs (the persistent kernel's pipeline holds two; an
-//    empty expert's window is all zeros, so its gradient comes out 0);
+//  - K windows: expert e owns positions koff[e] .. koff[e+1], its row count
+//    rounded up to a multiple of 64 (the K slab) and to at least two slabs
+//    (the persistent kernel's pipeline holds two; an empty expert's positions
+//    all read as zeros, so its gradient comes out 0);
 //  - work items: each window cut into pieces of at most kWgradSlabs slabs,
 //    split evenly (sizes differ by at most one slab, and every piece keeps
 //    at least two slabs, as a window does), so that no tile runs
@@ -73,7 +72,7 @@ __global__ __launch_bounds__(256) void k_transpose_w(const bf16_t* __restrict__ 
 //  - rlist: the split experts {e, first partial block, pieces}.
 // wcount[0] = items, wcount[1] = split experts.
 __global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__ offsets, int E,
-                                                    int32_t* __restrict__ koff, TileDesc* __restrict__ items,
+                                                    int32_t* __restrict__ koff, WgradItem* __restrict__ items,
                                                     TileDesc* __restrict__ rlist, int32_t* __restrict__ wcount) {
     __shared__ int32_t len[kMaxE], pieces[kMaxE], pfirst[kMaxE], rslot[kMaxE];
     __shared__ int32_t cursor[kWgradSlabs + 1];  // next item position per piece length (slabs)
@@ -135,11 +134,14 @@ __global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__
         int s0 = 0;
         for (int c = 0; c < n; ++c) {
             const int sz = base + (c < extra ? 1 : 0);
-            TileDesc t;
+            const int count = offsets[e + 1] - offsets[e];
+            WgradItem t{};
             t.e = e;
-            t.row0 = koff[e] + s0 * 64;
-            t.rows = sz * 64;
-            t.pad = pfirst[e] < 0 ? -1 : pfirst[e] + c;
+            t.q0 = koff[e] + s0 * 64;
+            t.klen = sz * 64;
+            t.dest = pfirst[e] < 0 ? -1 : pfirst[e] + c;
+            t.row0 = offsets[e] + s0 * 64;
+            t.rows = max(0, min(sz * 64, count - s0 * 64));
             const int p = atomicAdd(&cursor[sz], 1), b = p % kNumXcd;
             items[b * (nitems / kNumXcd) + min(b, nitems % kNumXcd) + p / kNumXcd] = t;
             s0 += sz;
@@ -173,109 +175,31 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
     }
 }
 
-// Transposing gather into the K windows: out[c][q] for window position q of
-// expert e (q = koff[e] + i) is in[src(offsets[e] + i)][c] when i < count_e,
-// and 0 in the padding up to the window's end. src(p) is p (rows already in
-// sorted order), row_map[p] (slot rows) or row_map[p] / K (token rows).
-// in: [rows, C] bf16; out: [C, ld] bf16 stored slab-major, [ld / 64][C][64]
-// (element (c, q) at ((q / 64) C + c) 64 + q % 64), so that one 64-column K
-// slab of a product's operand tile is contiguous. C a multiple of 64.
-// Positions past koff[E] are left alone.
-//
-// A workgroup moves one 64-position block across all C columns. Windows are
-// multiples of 64, so the block lies in one expert's window: one search per
-// workgroup. Lane (rg, cg) of a wave holds an 8 x 8 block, positions 8 rg ..
-// 8 rg + 7 and 8 columns: it loads 8 16-byte row pieces, transposes them in
-// registers and stores 8 16-byte column pieces. The 8 lanes of one cg cover a
-// whole 128-byte line both ways: 8 rows' 8 columns in, one column's 64
-// positions out. The 4 waves take 64-column quarters of each 256-column step.
-__device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b, bool high) {
-    return high ? (a >> 16) | (b & 0xFFFF0000u) : (a & 0xFFFFu) | (b << 16);
-}
-__device__ __forceinline__ uint32_t word_of(const uint4& v, int w) {
-    return w == 0 ? v.x : (w == 1 ? v.y : (w == 2 ? v.z : v.w));
-}
-
-__global__ __launch_bounds__(256) void k_transpose_window(const bf16_t* __restrict__ in, int C, int mode,
-                                                         const int32_t* __restrict__ row_map, int K,
-                                                         const int32_t* __restrict__ offsets,
-                                                         const int32_t* __restrict__ koff, int E,
-                                                         bf16_t* __restrict__ out) {
-    const int q0 = blockIdx.x * TT;
-    const int total = koff[E];
-    if (q0 >= total) return;  // uniform per workgroup
-    int lo = 0, hi = E - 1;   // last expert with koff[e] <= q0
+// Row tables of the weight-gradient products' gathered operands: window
+// position q of expert e (q = koff[e] + i) is sorted row offsets[e] + i, the
+// padding positions kWgradNoRow. One wave per 64 positions; windows are
+// multiples of 64, so they lie in one expert's window.
+__global__ __launch_bounds__(256) void k_wgrad_rows(const int32_t* __restrict__ sorted_slots,
+                                                   const int32_t* __restrict__ offsets,
+                                                   const int32_t* __restrict__ koff, int E, int K, uint32_t row_bytes,
+                                                   uint32_t* __restrict__ gtab, uint32_t* __restrict__ xtab) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= koff[E]) return;
+    int lo = 0, hi = E - 1;  // last expert with koff[e] <= q
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        if (koff[mid] <= q0) lo = mid;
+        if (koff[mid] <= q) lo = mid;
         else hi = mid - 1;
     }
-    const int base = offsets[lo], count = offsets[lo + 1] - base;
-    const int i0 = q0 - koff[lo];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int rg = lane & 7, cg = lane >> 3;
-    // Source rows of the lane's 8 positions (-1: padding, zeros).
-    int srow[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int i = i0 + rg * 8 + j;
-        int v = -1;
-        if (i < count) {
-            const int p = base + i;
-            v = mode == SRC_SORTED ? p : (mode == SRC_SLOT ? row_map[p] : row_map[p] / K);
-        }
-        srow[j] = v;
+    const int i = q - koff[lo], base = offsets[lo];
+    uint32_t g = kWgradNoRow, x = kWgradNoRow;
+    if (i < offsets[lo + 1] - base) {
+        const uint32_t slot = (uint32_t)sorted_slots[base + i];
+        g = slot * row_bytes;
+        x = slot / (uint32_t)K * row_bytes;
     }
-    bf16_t* const ob = out + (size_t)(q0 / TT) * C * TT + rg * 8;
-    for (int c = wave * 64 + cg * 8; c < C; c += 256) {
-        // Padding positions load row 0 (T >= 1, so it exists) and keep zeros:
-        // no branch, so all 8 loads are in flight together.
-        uint4 v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint4 t = *reinterpret_cast<const uint4*>(in + (size_t)(srow[j] < 0 ? 0 : srow[j]) * C + c);
-            v[j] = srow[j] >= 0 ? t : make_uint4(0u, 0u, 0u, 0u);
-        }
-        // Column k of the block: element k of each row, rows in pairs per word.
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int w = k >> 1;
-            const bool high = k & 1;
-            uint4 o;
-            o.x = pair16(word_of(v[0], w), word_of(v[1], w), high);
-            o.y = pair16(word_of(v[2], w), word_of(v[3], w), high);
-            o.z = pair16(word_of(v[4], w), word_of(v[5], w), high);
-            o.w = pair16(word_of(v[6], w), word_of(v[7], w), high);
-            store16_nt(ob + (size_t)(c + k) * TT, o);
-        }
-    }
-}
-
-// out[g][r][:] = in[g][src(r)][:] for the 2h stacked rows of a [G][2 ld][C]
-// fp32 tensor (src(r) = r for r < h, ld + r - h after): the padded weight
-// gradient of stacked gate and up rows back to the unpadded layout.
-__global__ __launch_bounds__(256) void k_compact_rows(const float* __restrict__ in, int G, int h, int ld, int C,
-                                                     float* __restrict__ out) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t q = C / 4;
-    if (i >= (size_t)G * 2 * h * q) return;
-    const size_t row = i / q, g = row / (2 * h);
-    const int r = (int)(row - g * 2 * h), c = (int)(i % q) * 4;
-    const int sr = r < h ? r : ld + r - h;
-    *reinterpret_cast<float4*>(out + row * C + c) =
-        *reinterpret_cast<const float4*>(in + (g * 2 * ld + sr) * (size_t)C + c);
-}
-
-// Zero the K window of every expert with no rows (its two slabs of the
-// slab-major operand [ld / 64][C][64]); one workgroup per expert.
-__global__ __launch_bounds__(256) void k_zero_empty_windows(bf16_t* __restrict__ out, int C,
-                                                           const int32_t* __restrict__ offsets,
-                                                           const int32_t* __restrict__ koff) {
-    const int e = blockIdx.x;
-    if (offsets[e + 1] != offsets[e]) return;
-    uint4* p = reinterpret_cast<uint4*>(out + (size_t)koff[e] * C);
-    const size_t n = (size_t)(koff[e + 1] - koff[e]) * C / 8;
-    for (size_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = make_uint4(0u, 0u, 0u, 0u);
+    gtab[q] = g;
+    xtab[q] = x;
 }
 
 __device__ __forceinline__ uint32_t pack2_bf16_rne(float lo, float hi) {
@@ -322,13 +246,7 @@ hipError_t launch_transpose_w13(const void* in, int G, int h, int ld, int C, voi
     return hipGetLastError();
 }
 
-hipError_t launch_compact_rows(const float* in, int G, int h, int ld, int C, float* out, hipStream_t s) {
-    const size_t n = (size_t)G * 2 * h * (C / 4);
-    hipLaunchKernelGGL(k_compact_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, in, G, h, ld, C, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, TileDesc* items, TileDesc* rlist,
+hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
                              int32_t* wcount, hipStream_t s) {
     hipLaunchKernelGGL(k_wgrad_plan, dim3(1), dim3(1024), 0, s, offsets, E, koff, items, rlist, wcount);
     return hipGetLastError();
@@ -342,17 +260,10 @@ hipError_t launch_wgrad_reduce(const float* partials, const TileDesc* rlist, con
     return hipGetLastError();
 }
 
-hipError_t launch_transpose_window(const void* in, int C, int mode, const int32_t* row_map, int K,
-                                   const int32_t* offsets, const int32_t* koff, int E, void* out, int ld,
-                                   hipStream_t s) {
-    hipLaunchKernelGGL(k_transpose_window, dim3(ld / TT), dim3(256), 0, s, static_cast<const bf16_t*>(in), C, mode,
-                       row_map, K, offsets, koff, E, static_cast<bf16_t*>(out));
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_empty_windows(void* out, int C, const int32_t* offsets, const int32_t* koff, int E,
-                                     hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_empty_windows, dim3(E), dim3(256), 0, s, static_cast<bf16_t*>(out), C, offsets, koff);
+hipError_t launch_wgrad_rows(const int32_t* sorted_slots, const int32_t* offsets, const int32_t* koff, int E, int K,
+                             uint32_t row_bytes, uint32_t* gtab, uint32_t* xtab, int ld, hipStream_t s) {
+    hipLaunchKernelGGL(k_wgrad_rows, dim3((unsigned)((ld + 255) / 256)), dim3(256), 0, s, sorted_slots, offsets, koff,
+                       E, K, row_bytes, gtab, xtab);
     return hipGetLastError();
 }
 

@@ -40,6 +40,22 @@
 #include <utility>
 
 namespace moe {
+// Workgroups of the persistent kernel: one per CU (a multiple of the XCD
+// count), fewer when the grid-sizing bound on the tiles is smaller.
+int persistent_grid(long long tile_bound) {
+    static int cus[64] = {0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+    if (cus[dev] == 0) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < kNumXcd)
+            n = 256;
+        cus[dev] = n / kNumXcd * kNumXcd;
+    }
+    const long long bound = (tile_bound + kNumXcd - 1) / kNumXcd * kNumXcd;
+    return (int)(bound < cus[dev] ? bound : cus[dev]);
+}
+
 namespace {
 
 __device__ __forceinline__ float gelu_erf(float v) {
@@ -96,31 +112,6 @@ __device__ __forceinline__ float swiglu_col(float g, float u, bool valid) {
     return valid ? silu_as(g) * u : 0.0f;
 }
 
-// Tile of workgroup `b` in the weight-gradient product: work items x (M / bm)
-// row tiles x (N / bn) column tiles, in the same XCD-aware order as
-// locate_tile (the tiles of one item are adjacent). M = a.dense_rows. tc.e is
-// the work item here.
-__device__ __forceinline__ TileCoord locate_wgrad_tile(const GemmArgs& a, int bm, int bn) {
-    TileCoord tc;
-    tc.valid = false;
-    const int n_n = a.N / bn;
-    const int m_per = a.dense_rows / bm;
-    const int total = *a.n_tiles * m_per * n_n;
-    const int per = (total + kNumXcd - 1) / kNumXcd;
-    const int b = blockIdx.x;
-    const int j = b / kNumXcd;
-    if (j >= per) return tc;
-    const int lid = (b % kNumXcd) * per + j;
-    if (lid >= total) return tc;
-    const int mt = lid / n_n;
-    tc.n0 = (lid - mt * n_n) * bn;
-    tc.e = mt / m_per;
-    tc.row0 = (mt - tc.e * m_per) * bm;
-    tc.rows = bm;
-    tc.valid = true;
-    return tc;
-}
-
 // Weight rows a tile may read: the group's rows (B rows past b_rows, when
 // set, read as zeros through the buffer-resource bound).
 __device__ __forceinline__ int weight_rows(const GemmArgs& a) { return a.b_rows > 0 ? a.b_rows : a.N; }
@@ -128,11 +119,6 @@ __device__ __forceinline__ int weight_rows(const GemmArgs& a) { return a.b_rows 
 // Epilogues of a first expert layer: their token rows are gathered from x.
 __host__ __device__ constexpr bool fc1_epi(int epi) {
     return epi == EPI_GELU_STORE || epi == EPI_SWIGLU_STORE || epi == EPI_SWIGLU_BWD;
-}
-// Epilogues of the persistent kernel that can also write their bf16 result
-// transposed into the weight-gradient windows (GemmArgs::CT).
-__host__ __device__ constexpr bool ct_epi(int epi) {
-    return epi == EPI_GELU_BWD || epi == EPI_SWIGLU_BWD || epi == EPI_DGELU;
 }
 
 // Derivative of gelu_sig, so that the backward differentiates the function
@@ -189,12 +175,11 @@ void k_gemm_bf16(const GemmArgs a) {
     static_assert(STAGES >= 2 && STAGES <= 5, "2 to 5 stages");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES * STAGE];
     __shared__ int32_t srow[BM];
-    constexpr bool WGRAD = EPI == EPI_WGRAD_F32;
     // A rows gathered through the row map (first layers, the backward's dA).
     constexpr bool A_GATHER = fc1_epi(EPI) || EPI == EPI_GELU_BWD || EPI == EPI_DGELU || EPI == EPI_DSWIGLU;
     // Output rows scattered to slot order (second layer, the backward's dx).
     constexpr bool O_SCATTER = EPI == EPI_SCATTER_SLOT || EPI == EPI_SCATTER_SLOT_F32;
-    const TileCoord tc = WGRAD ? locate_wgrad_tile(a, BM, BN) : locate_tile<GROUPED>(a, BM, BN);
+    const TileCoord tc = locate_tile<GROUPED>(a, BM, BN);
     if (!tc.valid) return;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -221,16 +206,12 @@ void k_gemm_bf16(const GemmArgs a) {
     const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.A, a.a_bytes);
     // SwiGLU: the group's 2 act_n weight rows; reads past them return zeros.
     const __amdgpu_buffer_rsrc_t wres =
-        make_rsrc(static_cast<const bf16_t*>(a.B) + (WGRAD ? 0 : (size_t)tc.e * a.b_group_stride),
+        make_rsrc(static_cast<const bf16_t*>(a.B) + (size_t)tc.e * a.b_group_stride,
                   (uint32_t)(SWIGLU ? 2 * a.act_n : weight_rows(a)) * Kd * 2);
 
     constexpr int SWZ_SHIFT = CPR == 8 ? 1 : 2;
     constexpr int SWZ_MASK = CPR - 1;
-    // Operand row stride. The weight-gradient operands are slab-major
-    // ([K / 64][rows][64]): a row's 64-column piece is 128 bytes after the
-    // previous row's, and a K slab is rows * 128 bytes.
-    static_assert(!WGRAD || BK == 64, "slab-major operands have 64-column slabs");
-    const uint32_t rstride = WGRAD ? 128u : (uint32_t)(Kd * 2);
+    const uint32_t rstride = (uint32_t)(Kd * 2);
 
     uint32_t xv[AP];
 #pragma unroll
@@ -283,16 +264,10 @@ void k_gemm_bf16(const GemmArgs a) {
         xoff[ks] = base + (wm * WTM) * ROWB + k;
         woff[ks] = base + BM * ROWB + (wn * WTN) * ROWB + k;
     }
-    // K range: the whole row, or (weight gradients) the group's window, or
-    // (split K, dense fp32 output) part blockIdx.y of gridDim.y equal parts.
+    // K range: the whole row, or (split K, dense fp32 output) part blockIdx.y of
+    // gridDim.y equal parts.
     int nk = Kd / BK;
     uint32_t kbase = 0;
-    TileDesc item{};
-    if (WGRAD) {
-        item = a.tiles[tc.e];
-        nk = item.rows / BK;
-        kbase = (uint32_t)item.row0 * 2;
-    }
     if constexpr (!GROUPED && EPI == EPI_STORE_F32) {
         nk /= (int)gridDim.y;
         kbase = (uint32_t)blockIdx.y * (uint32_t)nk * BK * 2;
@@ -300,22 +275,17 @@ void k_gemm_bf16(const GemmArgs a) {
 
     auto issue = [&](int stage, int kslab) {
         uint8_t* buf = smem + stage * STAGE;
-        uint32_t soff_a = kbase + (uint32_t)kslab * BK * 2, soff_b = soff_a;
-        if (WGRAD) {
-            const uint32_t slab = (uint32_t)(item.row0 / 64 + kslab);
-            soff_a = slab * (uint32_t)a.dense_rows * 128u;
-            soff_b = slab * (uint32_t)a.N * 128u;
-        }
+        const uint32_t soff = kbase + (uint32_t)kslab * BK * 2;
 #pragma unroll
-        for (int i = 0; i < AP; ++i) copy16_to_lds(xres, xv[i], soff_a, buf + (wave + NW * i) * 1024);
+        for (int i = 0; i < AP; ++i) copy16_to_lds(xres, xv[i], soff, buf + (wave + NW * i) * 1024);
 #pragma unroll
         for (int i = 0; i < BP; ++i) {
             // Weights read once in this launch (a.b_nt: one M-tile per expert
             // on average) stream past the caches.
             if (a.b_nt)
-                copy16_to_lds_nt(wres, wv[i], soff_b, buf + BM * ROWB + (wave + NW * i) * 1024);
+                copy16_to_lds_nt(wres, wv[i], soff, buf + BM * ROWB + (wave + NW * i) * 1024);
             else
-                copy16_to_lds(wres, wv[i], soff_b, buf + BM * ROWB + (wave + NW * i) * 1024);
+                copy16_to_lds(wres, wv[i], soff, buf + BM * ROWB + (wave + NW * i) * 1024);
         }
     };
     auto read_frags = [&](uint32_t sbase, int ks, bf16x8_t* xf, bf16x8_t* wf) {
@@ -384,7 +354,7 @@ void k_gemm_bf16(const GemmArgs a) {
     // The fused combine (dense, K <= 8) stages the shared expert's fp32 output.
     constexpr bool COMB = EPI == EPI_COMBINE;
     static_assert(!(COMB && GROUPED), "the fused combine is a dense (shared expert) epilogue");
-    constexpr bool OUT_F32 = EPI == EPI_STORE_F32 || EPI == EPI_SCATTER_SLOT_F32 || WGRAD || COMB;
+    constexpr bool OUT_F32 = EPI == EPI_STORE_F32 || EPI == EPI_SCATTER_SLOT_F32 || COMB;
     constexpr int OES = OUT_F32 ? 4 : 2;           // staged element size
     constexpr int SEG = (SWIGLU ? HW : WTN) * OES * (DSW ? 2 : 1);  // bytes of one wave-tile row
     constexpr int RSTR = SEG + 16;                 // padded LDS row stride
@@ -517,10 +487,6 @@ void k_gemm_bf16(const GemmArgs a) {
                 void* obase = a.C;
                 if constexpr (!GROUPED && EPI == EPI_STORE_F32)  // split K: this part's partial sums
                     obase = static_cast<float*>(a.C) + (size_t)blockIdx.y * a.dense_rows * a.N;
-                if (WGRAD) {  // the expert's gradient, or the item's partial block
-                    orow += (size_t)(item.pad < 0 ? item.e : item.pad) * a.dense_rows;
-                    if (item.pad >= 0) obase = a.C2;
-                }
                 size_t ocol = (size_t)ocol0;
                 int pcc = pc;
                 if (DSW && pc >= CPRO / 2) {  // the dU half goes act_ld columns further on
@@ -888,12 +854,8 @@ void k_gemm_pp(const GemmArgs a) {
     constexpr bool SWIGLU = EPI == EPI_SWIGLU_STORE || EPI == EPI_SWIGLU_BWD;
     constexpr bool SWBWD = EPI == EPI_SWIGLU_BWD;  // and the fp32 gate / up pre-activations into C2
     constexpr bool SCATTER = EPI == EPI_SCATTER_SLOT || EPI == EPI_SCATTER_SLOT_F32;
-    // Weight gradients: slab-major operands, a K window per work item, fp32
-    // output to the expert's gradient or a partial block.
-    constexpr bool WG = EPI == EPI_WGRAD_F32;
-    static_assert(!WG || GROUPED, "weight-gradient tiles come from the work-item table");
     constexpr bool RNORM = EPI == EPI_ROUTER_F32;  // EPI_STORE_F32 and the token rows' sums of squares
-    constexpr bool OUT_F32 = EPI == EPI_STORE_F32 || EPI == EPI_SCATTER_SLOT_F32 || WG || RNORM;
+    constexpr bool OUT_F32 = EPI == EPI_STORE_F32 || EPI == EPI_SCATTER_SLOT_F32 || RNORM;
     constexpr bool COMBINE = EPI == EPI_COMBINE;
     constexpr bool STAGE_F32 = OUT_F32 || COMBINE;  // accumulators staged as fp32
     constexpr int OES = OUT_F32 ? 4 : 2;
@@ -904,9 +866,7 @@ void k_gemm_pp(const GemmArgs a) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[AST * SLAB + WST * SLAB];
 
     const int n_n = a.N / BN;
-    const int m_per = WG ? a.dense_rows / BM : 1;  // row tiles per work item
-    const int total =
-        (GROUPED ? __builtin_amdgcn_readfirstlane(*a.n_tiles) * m_per : (a.dense_rows + BM - 1) / BM) * n_n;
+    const int total = (GROUPED ? __builtin_amdgcn_readfirstlane(*a.n_tiles) : (a.dense_rows + BM - 1) / BM) * n_n;
     const int per = (total + kNumXcd - 1) / kNumXcd;
     const int xcd = blockIdx.x % kNumXcd;
     const int wpx = gridDim.x / kNumXcd;  // workgroups per XCD: the tile stride
@@ -934,20 +894,17 @@ void k_gemm_pp(const GemmArgs a) {
     const int Kd = a.Kdim;
     const int nk = Kd / BK;
     const int ncols = a.ldc > 0 ? a.ldc : a.N;  // real output columns (N may be rounded up to BN)
-    // Slab-major operands (weight gradients): a row's piece of one K slab is
-    // 128 bytes after the previous row's.
-    const uint32_t rowbytes = WG ? 128u : (uint32_t)Kd * 2;
+    const uint32_t rowbytes = (uint32_t)Kd * 2;
 
     struct Tile {
         int e, row0, rows, n0;
-        int slab0, nk, dest;  // weight gradients: first K slab, K slabs, partial block or -1
     };
     // Tile-table entry of tile l (grouped): read through the vector path (the
     // kernel's own stores keep the compiler from proving the table constant).
     // Indices past this workgroup's share read its last tile instead.
     auto tile_entry = [&](int l) {
         TileDesc d{};
-        if (GROUPED) d = a.tiles[min(l, lid_end - 1) / n_n / m_per];
+        if (GROUPED) d = a.tiles[min(l, lid_end - 1) / n_n];
         return d;
     };
     // Tile l from its table entry; the entry is the same for every lane, so it
@@ -956,17 +913,7 @@ void k_gemm_pp(const GemmArgs a) {
         Tile t;
         const int mt = l / n_n;
         t.n0 = (l - mt * n_n) * BN;
-        t.slab0 = 0;
-        t.nk = nk;
-        t.dest = -1;
-        if (WG) {
-            t.e = __builtin_amdgcn_readfirstlane(d.e);
-            t.row0 = (mt - (mt / m_per) * m_per) * BM;
-            t.rows = BM;
-            t.slab0 = __builtin_amdgcn_readfirstlane(d.row0) / BK;
-            t.nk = __builtin_amdgcn_readfirstlane(d.rows) / BK;
-            t.dest = __builtin_amdgcn_readfirstlane(d.pad);
-        } else if (GROUPED) {
+        if (GROUPED) {
             t.e = __builtin_amdgcn_readfirstlane(d.e);
             t.row0 = __builtin_amdgcn_readfirstlane(d.row0);
             t.rows = __builtin_amdgcn_readfirstlane(d.rows);
@@ -990,24 +937,15 @@ void k_gemm_pp(const GemmArgs a) {
         if (SWIGLU)
             return make_rsrc(Bw + (size_t)t.e * a.b_group_stride + (size_t)(t.n0 / 2) * Kd,
                              (uint32_t)__builtin_amdgcn_readfirstlane(2 * a.act_n - t.n0 / 2) * rowbytes);
-        // Weight gradients: every K slab of rows n0 .. (slab-major operand).
-        if (WG) return make_rsrc(Bw + (size_t)t.n0 * 64, (uint32_t)ncols * (uint32_t)Kd * 2u - (uint32_t)t.n0 * 128u);
         const int rows = __builtin_amdgcn_readfirstlane(max(0, min(BN, weight_rows(a) - t.n0)));
         return make_rsrc(Bw + (size_t)t.e * a.b_group_stride + (size_t)t.n0 * Kd, (uint32_t)rows * rowbytes);
     };
     auto xres_of = [&](const Tile& t) {
         if (GATHER) return make_rsrc(Ax, a.a_bytes);
-        if (WG) return make_rsrc(Ax + (size_t)t.row0 * 64, a.a_bytes - (uint32_t)t.row0 * 128u);
         return make_rsrc(Ax + (size_t)t.row0 * Kd, (uint32_t)t.rows * rowbytes);
     };
-    // Source offset of K slab s of tile t: s slabs along the rows, or
-    // (slab-major) slab t.slab0 + s of rows x 128 bytes.
-    auto soff_a = [&](const Tile& t, int s) -> uint32_t {
-        return WG ? (uint32_t)(t.slab0 + s) * (uint32_t)a.dense_rows * 128u : (uint32_t)s * (BK * 2);
-    };
-    auto soff_b = [&](const Tile& t, int s) -> uint32_t {
-        return WG ? (uint32_t)(t.slab0 + s) * (uint32_t)ncols * 128u : (uint32_t)s * (BK * 2);
-    };
+    // Source offset of K slab s.
+    auto soff_of = [](int s) -> uint32_t { return (uint32_t)s * (BK * 2); };
     const __amdgpu_buffer_rsrc_t xnull = make_rsrc(Ax, 0);
     const __amdgpu_buffer_rsrc_t wnull = make_rsrc(Bw, 0);
 
@@ -1251,75 +1189,6 @@ void k_gemm_pp(const GemmArgs a) {
     // `stslot`: per 32-row block (and 64-column half for fp32 output) each
     // lane writes its row's runs into the wave's 8 KB, then reads back 16-byte
     // row pieces (16 lanes per 256-byte row) and stores whole lines.
-    // Backward: the staged bf16 block i (32 rows of this wave, ncc columns of
-    // the 256-byte staging rows) also goes to the weight-gradient K windows,
-    // transposed and slab-major: staged column cc becomes row colmap(cc) (or
-    // nothing for -1); rows past the tile's valid rows are written as 0 up to
-    // the window's end, rows past the window are not written. Window starts
-    // are multiples of 64 and tiles start 256 rows apart inside an expert, so
-    // each 8-row piece lies inside one 64-position slab.
-    constexpr bool HAS_CT = ct_epi(EPI);
-    auto store_ct = [&](const Tile& t, uint32_t stg, int i, int ncc, auto&& colmap) {
-        const int e = t.e;
-        const int gpos = t.row0 - a.goff[e] + wm * WT + i * 32;  // first row of the block within its expert
-        const int wq = a.koff[e] + gpos;
-        const int wlen = a.koff[e + 1] - a.koff[e];
-        const int vrows = t.rows - (wm * WT + i * 32);  // rows of the block that exist
-        uint8_t* const ct = static_cast<uint8_t*>(a.CT);
-        // Piece k of a lane: staged column cc = 16 k + lane % 16, rows 8 g ..
-        // 8 g + 7 with g = lane / 16, as two transposing 8-byte reads, the even
-        // rows 8 g, 8 g + 2, .. and the odd rows 8 g + 1, 8 g + 3, ..: in each
-        // read the 16 lanes of a quarter-wave name 4 rows x 16 columns (lane r:
-        // row r / 4 of the four, columns 4 (r % 4) ..) and each receives its
-        // column's 4 rows, which are then interleaved into the row order the
-        // window stores. Rows two apart keep the 16-byte pieces a quarter-wave
-        // reads in distinct banks under the staging swizzle. Two pieces in
-        // flight: the reads of piece k + 1 are issued before piece k is stored.
-        const int nit = ncc / 16;
-        // The lane index through an opaque copy: the per-piece addresses are
-        // then computed here instead of being hoisted out of the tile loop.
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
-        const int g = ln >> 4, c16 = ln & 15;
-        u32x2_t w[2][2];
-        auto issue = [&](int k, u32x2_t(&dst)[2]) {
-            const int col = 16 * k + 4 * (c16 & 3);
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int row = 8 * g + hh + 2 * (c16 >> 2);
-                lds_read_tr8_asm(dst[hh], stg + (uint32_t)row * 256u +
-                                              ((uint32_t)((col >> 3) ^ (row & 15)) << 4) + (uint32_t)(col & 7) * 2u);
-            }
-        };
-        issue(0, w[0]);
-#pragma unroll
-        for (int k = 0; k < nit; ++k) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (k + 1 < nit) {
-                issue(k + 1, w[(k + 1) & 1]);
-                wait_lgkmcnt<2>();
-            } else {
-                wait_lgkmcnt0();
-            }
-            tie(w[k & 1][0]);
-            tie(w[k & 1][1]);
-            const int orow = colmap(16 * k + c16);
-            if (orow < 0 || gpos + g * 8 >= wlen) continue;
-            const u32x2_t ev = w[k & 1][0], od = w[k & 1][1];  // rows 0, 2, 4, 6 and 1, 3, 5, 7 of the piece
-            u32x4_t v = {(ev.x & 0xffffu) | (od.x << 16), (ev.x >> 16) | (od.x & 0xffff0000u),
-                         (ev.y & 0xffffu) | (od.y << 16), (ev.y >> 16) | (od.y & 0xffff0000u)};
-            if (vrows < 32) {  // the expert's last rows: zeros past them
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (g * 8 + 2 * u >= vrows) v[u] &= 0xffff0000u;
-                    if (g * 8 + 2 * u + 1 >= vrows) v[u] &= 0x0000ffffu;
-                }
-            }
-            const int q = wq + g * 8;
-            store16_asm(ct + (((size_t)(q / 64) * a.ct_cols + orow) * 64 + q % 64) * 2, v);
-        }
-    };
-
     auto epilogue = [&](const Tile& t, int stslot) {
         const uint32_t stg = base + (uint32_t)stslot * SLAB + (uint32_t)wave * STG_WAVE;
         const uint32_t wrow = stg + (uint32_t)fr * 256u;
@@ -1441,13 +1310,6 @@ void k_gemm_pp(const GemmArgs a) {
                     combine_block(t, stg, i, h);
                     continue;
                 }
-                if constexpr (SWBWD) {
-                    if (a.CT) {  // the activation only feeds dW2: its transpose alone
-                        const int ocol = t.n0 / 2 + wn * (WT / 2);
-                        store_ct(t, stg, i, WT / 2, [&](int cc) { return ocol < a.act_ld ? ocol + cc : -1; });
-                        continue;
-                    }
-                }
                 if constexpr (SWIGLU) {
                     // 128-byte activation rows: 8 lanes per row, 8 rows per read.
                     const int ocol = t.n0 / 2 + wn * (WT / 2);
@@ -1468,13 +1330,6 @@ void k_gemm_pp(const GemmArgs a) {
                     }
                     continue;
                 }
-                if constexpr (HAS_CT && !SWIGLU) {
-                    if (a.CT) {
-                        const int c0 = t.n0 + wn * WT + h * 64;
-                        store_ct(t, stg, i, WT, [&](int cc) { return c0 + cc; });
-                        if constexpr (BWD1) continue;  // the activation only feeds dW2
-                    }
-                }
                 u32x4_t v[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
@@ -1493,14 +1348,9 @@ void k_gemm_pp(const GemmArgs a) {
                     const int pcol = DSW ? (lane & 7) * 8 : (lane & 15) * (16 / OES);
                     const int col = t.n0 + wn * WT + h * 64 + pcol;
                     if (r < t.rows && t.n0 + wn * WT + h * 64 < ncols && (!DSW || col < a.act_ld)) {
-                        size_t orw = SCATTER ? (size_t)orow[i][k] : (size_t)(t.row0 + r);
-                        uint8_t* ob = cbase;
-                        if (WG) {  // the expert's gradient, or the work item's partial block
-                            orw += (size_t)(t.dest < 0 ? t.e : t.dest) * a.dense_rows;
-                            if (t.dest >= 0) ob = static_cast<uint8_t*>(a.C2);
-                        }
-                        uint8_t* out = ob + (orw * ostr + t.n0 + wn * WT + h * 64) * OES + (lane & 15) * 16;
-                        if (DSW) out = ob + (orw * ostr + ((lane & 8) ? a.act_ld : 0) + col) * 2;
+                        const size_t orw = SCATTER ? (size_t)orow[i][k] : (size_t)(t.row0 + r);
+                        uint8_t* out = cbase + (orw * ostr + t.n0 + wn * WT + h * 64) * OES + (lane & 15) * 16;
+                        if (DSW) out = cbase + (orw * ostr + ((lane & 8) ? a.act_ld : 0) + col) * 2;
                         store16_asm(out, v[k]);
                     }
                 }
@@ -1587,10 +1437,10 @@ void k_gemm_pp(const GemmArgs a) {
 
     // Prologue: token slab 0, weight slab 0, token slab 1, the first half of
     // weight slab 1; wait for slab 0 of both operands; read its first fragments.
-    static_for<AP>([&](auto LC) { copy_a(LC, 0, soff_a(tc, 0), xres_c, GATHER ? xv_c : tv); });
-    static_for<BP>([&](auto LC) { copy_w(LC, 0, soff_b(tc, 0), wres_c); });
-    static_for<AP>([&](auto LC) { copy_a(LC, 1, soff_a(tc, 1), xres_c, GATHER ? xv_c : tv); });
-    static_for<BP / 2>([&](auto LC) { copy_w(LC, 1, soff_b(tc, 1), wres_c); });
+    static_for<AP>([&](auto LC) { copy_a(LC, 0, soff_of(0), xres_c, GATHER ? xv_c : tv); });
+    static_for<BP>([&](auto LC) { copy_w(LC, 0, soff_of(0), wres_c); });
+    static_for<AP>([&](auto LC) { copy_a(LC, 1, soff_of(1), xres_c, GATHER ? xv_c : tv); });
+    static_for<BP / 2>([&](auto LC) { copy_w(LC, 1, soff_of(1), wres_c); });
     wait_vmcnt<AP + BP / 2>();
     barrier_no_fence();
     static_for<2 * FB>([&](auto QC) { read_frag(std::integral_constant<int, 0>{}, QC, 0u, 0u, 0); });
@@ -1603,11 +1453,9 @@ void k_gemm_pp(const GemmArgs a) {
             const int as1 = as == AST - 1 ? 0 : as + 1, as2 = as1 == AST - 1 ? 0 : as1 + 1;
             const int ws1 = ws ^ 1;
             // Slabs kt + 1 and kt + 2 may belong to the next tile.
-            const int nkc = tc.nk;
-            const bool n1 = kt + 1 >= nkc, n2 = kt + 2 >= nkc;
-            const uint32_t so1 = soff_b(n1 ? tn : tc, n1 ? kt + 1 - nkc : kt + 1);
-            const uint32_t so2 = soff_a(n2 ? tn : tc, n2 ? kt + 2 - nkc : kt + 2);
-            const uint32_t so2w = soff_b(n2 ? tn : tc, n2 ? kt + 2 - nkc : kt + 2);
+            const bool n1 = kt + 1 >= nk, n2 = kt + 2 >= nk;
+            const uint32_t so1 = soff_of(n1 ? kt + 1 - nk : kt + 1);
+            const uint32_t so2 = soff_of(n2 ? kt + 2 - nk : kt + 2);
             const __amdgpu_buffer_rsrc_t wr1 = n1 ? wres_n : wres_c;
             const __amdgpu_buffer_rsrc_t xr2 = n2 ? xres_n : xres_c;
             const __amdgpu_buffer_rsrc_t wr2 = n2 ? wres_n : wres_c;
@@ -1637,11 +1485,11 @@ void k_gemm_pp(const GemmArgs a) {
             // K step 3: first fragments of slab kt + 1; first half of weight
             // slab kt + 2 into the weight slot of slab kt.
             kstep(std::integral_constant<int, 1>{}, (uint32_t)as1 * SLAB, (uint32_t)ws1 * SLAB, 0, [&](auto CC) {
-                copy_w(std::integral_constant<int, decltype(CC)::value>{}, ws, so2w, wr2);
+                copy_w(std::integral_constant<int, decltype(CC)::value>{}, ws, so2, wr2);
             });
             as = as1;
             ws = ws1;
-        } while (++kt < tc.nk);
+        } while (++kt < nk);
 
         // The last K step also read the next tile's first fragments; let them
         // land (their registers are reused by the epilogue) and read them again
@@ -1864,7 +1712,6 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const GemmArgs a) {
 
 template <int BM, int BN, int WM, int WN, int BK, int ST, int WPE, int EPI, bool GROUPED>
 hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
-    if (a.CT) return hipErrorInvalidValue;  // transposed outputs exist on the persistent kernel only
     const int n_n = a.N / BN;
     const long long total = (long long)a.max_tiles * n_n;
     const long long grid = (total + kNumXcd - 1) / kNumXcd * kNumXcd;
@@ -1876,25 +1723,8 @@ hipError_t launch_bf16(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Workgroups of the persistent kernel: one per CU (a multiple of the XCD
-// count), fewer when the grid-sizing bound on the tiles is smaller.
-int persistent_grid(long long tile_bound) {
-    static int cus[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    if (cus[dev] == 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < kNumXcd)
-            n = 256;
-        cus[dev] = n / kNumXcd * kNumXcd;
-    }
-    const long long bound = (tile_bound + kNumXcd - 1) / kNumXcd * kNumXcd;
-    return (int)(bound < cus[dev] ? bound : cus[dev]);
-}
-
 template <int EPI, bool GROUPED, int KC = 8>
 hipError_t launch_pp(const GemmArgs& a, hipStream_t s) {
-    if (a.CT && !ct_epi(EPI)) return hipErrorInvalidValue;
     const int grid = persistent_grid((long long)a.max_tiles * (a.N / 256));
     hipLaunchKernelGGL((k_gemm_pp<EPI, GROUPED, KC>), dim3((unsigned)grid), dim3(256), 0, s, a);
     return hipGetLastError();
@@ -1987,15 +1817,6 @@ hipError_t dispatch_tiled(int bm, const GemmArgs& a, hipStream_t s) {
             p.N = (a.act_ld + 255) / 256 * 256;
             return launch_pp<EPI, GROUPED>(p, s);
         }
-    // Weight gradients: every work item spans at least two K slabs; N is
-    // rounded up to the tile width (B rows past N only feed unstored columns).
-    if constexpr (EPI == EPI_WGRAD_F32)
-        if (bm == 256 && a.dense_rows % 256 == 0) {
-            GemmArgs p = a;
-            p.ldc = a.N;
-            p.N = (a.N + 255) / 256 * 256;
-            return launch_pp<EPI, GROUPED>(p, s);
-        }
     if (bm == 256) {
         if (a.N % 128 == 0) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI, GROUPED>(a, s);
         return launch_bf16<256, 64, 4, 1, 64, 2, 1, EPI, GROUPED>(a, s);
@@ -2054,9 +1875,6 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
             case EPI_SCATTER_SLOT_F32:
                 if (GROUPED) return dispatch_tiled<EPI_SCATTER_SLOT_F32, true>(bm, a, s);
                 break;
-            case EPI_WGRAD_F32:
-                if (GROUPED && a.dense_rows % bm == 0) return dispatch_tiled<EPI_WGRAD_F32, true>(bm, a, s);
-                break;
             case EPI_SWIGLU_BWD:
                 if (GROUPED) return dispatch_swiglu_bwd(bm, a, s);
                 break;
@@ -2109,14 +1927,6 @@ int gemm_dense_bm(int32_t dtype, int64_t rows, int32_t n) {
     // 256-row tiles only when they still give a few workgroups per CU.
     const int64_t tiles = (rows + 255) / 256 * (n / 256 > 0 ? n / 256 : 1);
     return tiles >= 512 ? 256 : 64;
-}
-
-bool gemm_backward_transposed(const moe_desc_t& d, int bm) {
-    // The same conditions under which dispatch_tiled / dispatch_swiglu_bwd pick
-    // the persistent kernel for the recompute (K = d) and dA (K = d) products.
-    if (d.dtype != MOE_BF16 || bm != 256 || d.d < 128) return false;
-    if (d.flags & MOE_FLAG_SWIGLU) return true;  // widths rounded up to the tile
-    return d.h % 256 == 0;
 }
 
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim) {

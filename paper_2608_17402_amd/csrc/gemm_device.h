@@ -163,8 +163,9 @@ __device__ __forceinline__ void tie(uint32_t& v) { asm volatile("" : "+v"(v)); }
 // receives M[i / 4 + 4 j][i % 4] as its 16-bit element j (j = 0..3). With
 // lane r pointing at row r / 4 and columns 4 (r % 4) .. of a 4 x 16 block,
 // lane i gets column i of the 4 rows, row j in element j.
+template <int OFF>
 __device__ __forceinline__ void lds_read_tr8_asm(u32x2_t& r, uint32_t addr) {
-    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(r) : "v"(addr));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
 }
 __device__ __forceinline__ void tie(u32x2_t& v) { asm volatile("" : "+v"(v)); }
 // Two words 8 bytes apart (the two fp32 MFMAs' operands in a 16-byte chunk).

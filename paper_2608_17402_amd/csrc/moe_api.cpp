@@ -86,8 +86,9 @@ moe_status_t check_desc(const moe_desc_t* d) {
     return MOE_OK;
 }
 
-// The backward supports bf16 layers (GELU or SwiGLU experts); its transposed
-// operands and slot gradients are addressed through 32-bit buffer offsets.
+// The backward supports bf16 layers (GELU or SwiGLU experts); its gathered
+// operands and slot gradients are addressed through 32-bit buffer offsets, and
+// the margin of ld (192 rows or more) keeps kWgradNoRow past their ends.
 moe_status_t check_backward_desc(const moe_desc_t* d) {
     const moe_status_t st = check_desc(d);
     if (st != MOE_OK) return st;
@@ -96,7 +97,7 @@ moe_status_t check_backward_desc(const moe_desc_t* d) {
     const uint64_t ld = TK + 128 * (uint64_t)d->E + 64;
     const uint64_t hw = (uint64_t)act_stride(*d, d->h) * ((d->flags & MOE_FLAG_SWIGLU) ? 2 : 1);
     if (TK * d->d * 2 >= lim || TK * hw * 2 >= lim || (uint64_t)(d->d > hw ? d->d : hw) * ld * 2 >= lim)
-        return fail(MOE_ERR_UNSUPPORTED, "the backward's slot or transposed operands exceed 4 GiB");
+        return fail(MOE_ERR_UNSUPPORTED, "the backward's slot or windowed operands exceed 4 GiB");
     return MOE_OK;
 }
 
@@ -243,16 +244,13 @@ BackwardPlan plan_backward(const moe_desc_t& d) {
     b.dh = take(TK * hw * 2);
     b.dxs = take(TK * d.d * 4);
     b.koff = take(((size_t)d.E + 1) * 4);
-    b.gt = take((size_t)d.d * b.ld * 2);
-    b.at = take(hh * b.ld * 2);
-    b.dht = take(hw * b.ld * 2);
-    b.xt = take((size_t)d.d * b.ld * 2);
+    b.gtab = take((size_t)b.ld * 4);
+    b.xtab = take((size_t)b.ld * 4);
     b.items_max = d.E + (int32_t)(((size_t)b.ld / 64 + kWgradSlabs - 1) / kWgradSlabs);
-    b.items = take((size_t)b.items_max * sizeof(TileDesc));
+    b.items = take((size_t)b.items_max * sizeof(WgradItem));
     b.rlist = take((size_t)d.E * sizeof(TileDesc));
     b.wcount = take(16);
     b.partials = take((size_t)b.items_max * d.d * hw * 4);
-    b.dw1p = (sw && b.hh != d.h) ? take((size_t)d.E * hw * d.d * 4) : 0;
     b.total = off;
     return b;
 }
@@ -405,7 +403,7 @@ static moe_status_t enqueue_shared_mlp(const moe_desc_t& d, const WorkspacePlan&
 // GELU'(P) (SwiGLU: dG and dU from G and U), formed in that product's epilogue
 // with Gout the output gradients gathered by slot; the slot gradients of x are
 // dH W1 (fp32, slot order) summed per token; the weight gradients are
-// K-windowed products of slab-major transposed operands.
+// products over each expert's rows of the row-major tensors.
 static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b, void* ws, const void* x,
                                      const int32_t* sorted_slots, const int32_t* offsets, const void* w1,
                                      const void* w2, const void* gout, void* dx, float* dw1, float* dw2,
@@ -424,18 +422,15 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     float* dxs = region<float>(ws, b.dxs);
     int32_t* koff = region<int32_t>(ws, b.koff);
     HIP_CHECK(launch_build_tiles(d.E, p.tile_bm, p.max_tiles, offsets, tiles, ntiles, s), "build_tiles");
-    // Weight-gradient windows first: on the persistent kernel the recompute
-    // and dA products write the transposed activation and dH into them.
-    void* gt = region<void>(ws, b.gt);
-    void* at = region<void>(ws, b.at);
-    void* dht = region<void>(ws, b.dht);
-    void* xt = region<void>(ws, b.xt);
-    TileDesc* items = region<TileDesc>(ws, b.items);
+    uint32_t* gtab = region<uint32_t>(ws, b.gtab);
+    uint32_t* xtab = region<uint32_t>(ws, b.xtab);
+    WgradItem* items = region<WgradItem>(ws, b.items);
     TileDesc* rlist = region<TileDesc>(ws, b.rlist);
     int32_t* wcount = region<int32_t>(ws, b.wcount);
     float* partials = region<float>(ws, b.partials);
     HIP_CHECK(launch_wgrad_plan(offsets, d.E, koff, items, rlist, wcount, s), "weight-gradient plan");
-    const bool direct_t = gemm_backward_transposed(d, p.tile_bm);
+    HIP_CHECK(launch_wgrad_rows(sorted_slots, offsets, koff, d.E, d.K, (uint32_t)d.d * 2, gtab, xtab, b.ld, s),
+              "weight-gradient rows");
     if (sw) HIP_CHECK(launch_transpose_w13(w1, d.E, d.h, hh, d.d, w1t, s), "transpose w13");
     else HIP_CHECK(launch_transpose_w(w1, d.E, d.h, d.d, w1t, s), "transpose w1");
     HIP_CHECK(launch_transpose_w(w2, d.E, d.d, hh, w2t, s), "transpose w2");
@@ -457,12 +452,6 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     g.a_bytes = (uint32_t)((size_t)d.T * d.d * 2);
     g.act_n = d.h;
     g.act_ld = hh;
-    if (direct_t) {
-        g.CT = at;
-        g.ct_cols = hh;
-        g.koff = koff;
-        g.goff = offsets;
-    }
     HIP_CHECK(launch_gemm(d, sw ? EPI_SWIGLU_BWD : EPI_GELU_BWD, p.tile_bm, g, s), "backward fc1");
 
     GemmArgs ga = g;  // dH from Gout W2 and the pre-activations
@@ -475,12 +464,6 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     ga.b_group_stride = (int64_t)hh * d.d;
     ga.row_mode = ROWS_GATHER_SLOTS;
     ga.a_bytes = (uint32_t)(TK * d.d * 2);
-    // SwiGLU dA keeps its row output only: its epilogue already carries the
-    // fp32 gate and up reads, and a second, transposed output costs more
-    // there than the separate gather of dH.
-    const bool direct_dh = direct_t && !sw;
-    ga.CT = direct_dh ? dht : nullptr;
-    ga.ct_cols = hw;
     HIP_CHECK(launch_gemm(d, sw ? EPI_DSWIGLU : EPI_DGELU, p.tile_bm, ga, s), "backward dA");
 
     GemmArgs gx = g;  // slot gradients of x: dH W1, fp32 to slot order
@@ -493,54 +476,32 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     gx.b_group_stride = (int64_t)d.d * hw;
     gx.row_mode = ROWS_IDENTITY;
     gx.a_bytes = (uint32_t)(TK * hw * 2);
-    gx.CT = nullptr;
     HIP_CHECK(launch_gemm(d, EPI_SCATTER_SLOT_F32, p.tile_bm, gx, s), "backward dx");
     HIP_CHECK(launch_slot_sum(dxs, d.T, d.K, d.d, dx, s), "slot sum");
 
-    // Weight gradients: transposed operands in per-expert K windows (the
-    // activation and dH ones written above when the products ran persistent).
-    HIP_CHECK(launch_transpose_window(gout, d.d, SRC_SLOT, sorted_slots, d.K, offsets, koff, d.E, gt, b.ld, s),
-              "transpose G");
-    if (direct_t)
-        HIP_CHECK(launch_zero_empty_windows(at, hh, offsets, koff, d.E, s), "empty windows");
-    else
-        HIP_CHECK(launch_transpose_window(act, hh, SRC_SORTED, sorted_slots, d.K, offsets, koff, d.E, at, b.ld, s),
-                  "transpose A");
-    if (direct_dh)
-        HIP_CHECK(launch_zero_empty_windows(dht, hw, offsets, koff, d.E, s), "empty windows");
-    else
-        HIP_CHECK(launch_transpose_window(dh, hw, SRC_SORTED, sorted_slots, d.K, offsets, koff, d.E, dht, b.ld, s),
-                  "transpose dH");
-    HIP_CHECK(launch_transpose_window(x, d.d, SRC_TOKEN, sorted_slots, d.K, offsets, koff, d.E, xt, b.ld, s),
-              "transpose x");
-    auto wgrad = [&](const void* pa, int m, const void* pb, int n, float* out, const char* what) -> moe_status_t {
-        GemmArgs w{};
+    // Weight gradients: dW2 = Gout^T act (Gout gathered by slot), dW1 = dH^T x
+    // (x gathered by token), per-expert windows of rows.
+    auto wgrad = [&](bool gather_a, const void* pa, int m, const void* pb, int n, int half, float* out,
+                     const char* what) -> moe_status_t {
+        WgradArgs w{};
         w.A = pa;
         w.B = pb;
-        w.C = out;
-        w.dense_rows = m;
+        w.tab = gather_a ? gtab : xtab;
+        w.items = items;
+        w.n_items = wcount;
+        w.out = out;
+        w.partials = partials;
+        w.M = m;
         w.N = n;
-        w.Kdim = b.ld;
-        w.route_k = 1;
-        w.row_mode = ROWS_IDENTITY;
-        w.tiles = items;
-        w.n_tiles = wcount;
-        w.C2 = partials;
-        const int bm = m % 256 == 0 ? 256 : 64;
-        w.max_tiles = b.items_max * (m / bm);
-        w.a_bytes = (uint32_t)((size_t)m * b.ld * 2);
-        HIP_CHECK(launch_gemm(d, EPI_WGRAD_F32, bm, w, s), what);
-        HIP_CHECK(launch_wgrad_reduce(partials, rlist, wcount, d.E, (size_t)m * n, out, s), what);
+        w.h = half;
+        w.items_max = b.items_max;
+        w.gather_bytes = (uint32_t)((gather_a ? TK : (size_t)d.T) * d.d * 2);
+        HIP_CHECK(launch_wgrad(w, gather_a, s), what);
+        HIP_CHECK(launch_wgrad_reduce(partials, rlist, wcount, d.E, (size_t)(half ? 2 * half : m) * n, out, s), what);
         return MOE_OK;
     };
-    CHECK(wgrad(gt, d.d, at, hh, dw2, "dW2"));
-    if (b.dw1p) {  // SwiGLU with padded halves: compute padded, then drop the padding rows
-        float* dw1p = region<float>(ws, b.dw1p);
-        CHECK(wgrad(dht, hw, xt, d.d, dw1p, "dW13"));
-        HIP_CHECK(launch_compact_rows(dw1p, d.E, d.h, hh, d.d, dw1, s), "dW13 rows");
-    } else {
-        CHECK(wgrad(dht, hw, xt, d.d, dw1, "dW1"));
-    }
+    CHECK(wgrad(true, gout, d.d, act, hh, 0, dw2, "dW2"));
+    CHECK(wgrad(false, dh, hw, x, d.d, sw ? d.h : 0, dw1, "dW1"));
     return MOE_OK;
 }
 

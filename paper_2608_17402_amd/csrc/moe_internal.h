@@ -54,11 +54,6 @@ enum GemmEpilogue : int {
     EPI_GELU_BWD = 5,       // C[p, :] = bf16(GELU(acc)) and C2[p, :] = acc (fp32), sorted order
     EPI_DGELU = 6,          // C[p, :] = bf16(acc * GELU'(aux[p, :])) (aux fp32 [rows, N]), sorted order
     EPI_SCATTER_SLOT_F32 = 7,  // C[sorted_slots[p], :] = acc as fp32
-    EPI_WGRAD_F32 = 8,      // weight gradients (fp32): A [dense_rows, Kdim] and B [N, Kdim], stored
-                            // slab-major ([Kdim / 64][rows][64]), are shared by all experts; work item
-                            // i = tiles[i] = {e, k0, klen, dest} sums K columns
-                            // k0 .. k0 + klen (multiples of 64) of rows m into C[e][m, :] (dest < 0) or into
-                            // the partial block C2[dest] [dense_rows, N]; *n_tiles items
     // Backward of SwiGLU experts (tiled kernel only):
     EPI_SWIGLU_BWD = 9,     // EPI_SWIGLU_STORE, and the fp32 gate and up pre-activations into C2
                             // [rows, 2 act_ld]: G at column c, U at column act_ld + c
@@ -87,19 +82,9 @@ struct GemmArgs {
     int64_t b_group_stride;    // elements between consecutive experts' weights
     int32_t b_rows;            // dense bf16 only: rows of B that exist (0 = N); rows past them read as zeros
     uint32_t a_bytes;          // bytes of the A operand buffer (bounds of its buffer resource)
-    void* C2;                  // EPI_GELU_BWD: second output (fp32); EPI_WGRAD_F32: partial blocks;
-                               // EPI_ROUTER_F32: the rows' sums of squares [dense_rows] (fp32)
-    // Backward, persistent kernel: the bf16 output (the activation, or dH) also
-    // written transposed into the weight-gradient K windows, slab-major
-    // [windows / 64][ct_cols][64]: sorted position p of expert e goes to window
-    // position koff[e] + p - goff[e]; padding positions of the window get 0.
-    // EPI_GELU_BWD / EPI_SWIGLU_BWD then skip the row-major activation.
-    void* CT;
-    int32_t ct_cols;
-    const int32_t* koff;       // [E + 1] window starts
-    const int32_t* goff;       // [E + 1] group offsets (sorted positions)
+    void* C2;                  // EPI_GELU_BWD, EPI_SWIGLU_BWD: second output (fp32); EPI_ROUTER_F32: the rows' sums of squares [dense_rows] (fp32)
     const void* aux;           // EPI_DGELU: the pre-activation (fp32, rows of N); EPI_DSWIGLU: G, U
-    int32_t ldc;               // persistent kernel, EPI_WGRAD_F32 / EPI_DSWIGLU: the real column count when N
+    int32_t ldc;               // persistent kernel, EPI_DSWIGLU: the real column count when N
                                // is rounded up to the tile width (0 = N); columns past it are not stored
     int32_t act_n;             // EPI_SWIGLU_STORE: activation width h (valid columns)
     int32_t act_ld;            // EPI_SWIGLU_STORE: activation row stride (h rounded up to 128)
@@ -141,13 +126,12 @@ struct BackwardPlan {
     size_t dh;               // pre-activation gradient [T*K, hw] bf16, sorted order
     size_t dxs;              // slot gradients of x [T*K, d] fp32, slot order
     size_t koff;             // [E + 1] K-window starts
-    size_t gt, at, dht, xt;  // transposed operands [d | hh | hw, ld] bf16
-    size_t items, rlist;     // weight-gradient work items and split experts (TileDesc each)
+    size_t gtab, xtab;       // byte offsets of the window positions' rows in Gout and x [ld] (uint32)
+    size_t items, rlist;     // weight-gradient work items (WgradItem) and split experts (TileDesc)
     size_t wcount;           // [4] int32: item count, split-expert count
     size_t partials;         // [items_max, d, hw] fp32 partial sums of split experts
-    size_t dw1p;             // SwiGLU with h < ldh: padded [E, hw, d] fp32 first-layer gradient, else 0
     int32_t hh, hw;
-    int32_t ld;              // row length of the transposed operands: T*K + 128 E, rounded up to 64
+    int32_t ld;              // bound on the window positions: T*K + 128 E, rounded up to 64
     int32_t items_max;       // bound on the work items (and on the partial blocks)
     size_t total;
 };
@@ -199,26 +183,50 @@ hipError_t launch_build_tiles(int32_t E, int32_t bm, int32_t max_tiles, const in
 hipError_t launch_gemm(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a, hipStream_t s);
 // Whether launch_gemm(EPI_COMBINE) supports this dense GEMM (M-tile bm, N columns, K = kdim).
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim);
-// Whether the backward's first-layer recompute and dA products run on the
-// persistent kernel (which can also write their transposed outputs).
-bool gemm_backward_transposed(const moe_desc_t& d, int bm);
-// Backward data movement (backward.hip). Row sources of the transposing
-// gather: rows already in sorted order, slot rows, token rows.
-enum TransposeSource : int { SRC_SORTED = 0, SRC_SLOT = 1, SRC_TOKEN = 2 };
+// Backward data movement (backward.hip).
 hipError_t launch_transpose_w(const void* in, int G, int R, int C, void* out, hipStream_t s);
 // Stacked gate/up weights [G][2h][C] -> [G][C][2 ld], rows padded to ld each.
 hipError_t launch_transpose_w13(const void* in, int G, int h, int ld, int C, void* out, hipStream_t s);
-// [G][2 ld][C] fp32 with padded gate/up halves -> [G][2h][C].
-hipError_t launch_compact_rows(const float* in, int G, int h, int ld, int C, float* out, hipStream_t s);
 // Longest K window of one weight-gradient work item, in 64-column slabs.
 constexpr int kWgradSlabs = 128;
-hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, TileDesc* items, TileDesc* rlist,
+// One work item of the weight-gradient products: klen window positions from
+// q0 (multiples of 64, at least two slabs) of expert e, whose rows are the sorted rows
+// row0 .. row0 + rows - 1 (rows <= klen; the positions past them are padding).
+// Its sums go to the expert's gradient (dest < 0) or to partial block dest.
+struct WgradItem {
+    int32_t e, q0, klen, dest;
+    int32_t row0, rows, pad0, pad1;
+};
+// Table entry of a padding position: past the end of every gathered operand
+// (check_backward_desc keeps them under 2^32 - 384 * 64 bytes), also with the
+// up to 511 bytes a 256-column tile adds.
+constexpr uint32_t kWgradNoRow = 0xFFFFFE00u;
+struct WgradArgs {
+    const void* A;            // bf16 rows of M elements
+    const void* B;            // bf16 rows of N elements
+    const uint32_t* tab;      // byte offset of the gathered operand's row per window position
+    const WgradItem* items;
+    const int32_t* n_items;
+    float* out;               // [E][M][N], or [E][2 h][N] with h > 0
+    float* partials;          // blocks of one expert's gradient
+    int32_t M, N;             // multiples of 64
+    int32_t h;                // > 0: A holds gate and up columns, M / 2 each, of which h exist
+    int32_t items_max;        // bound on the work items (grid sizing)
+    uint32_t gather_bytes;    // bytes of the gathered operand
+};
+// dW = A^T B per expert (wgrad.hip): A gathered and B in sorted order
+// (gather_a), or the other way round.
+hipError_t launch_wgrad(const WgradArgs& a, bool gather_a, hipStream_t s);
+// Workgroups of a persistent kernel with at most tile_bound tiles.
+int persistent_grid(long long tile_bound);
+hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
                              int32_t* wcount, hipStream_t s);
 hipError_t launch_wgrad_reduce(const float* partials, const TileDesc* rlist, const int32_t* wcount, int E,
                                size_t mn, float* out, hipStream_t s);
-hipError_t launch_transpose_window(const void* in, int C, int mode, const int32_t* row_map, int K,
-                                   const int32_t* offsets, const int32_t* koff, int E, void* out, int ld,
-                                   hipStream_t s);
+// Byte offsets of every window position's row in the slot rows (slot *
+// row_bytes) and the token rows (slot / K * row_bytes).
+hipError_t launch_wgrad_rows(const int32_t* sorted_slots, const int32_t* offsets, const int32_t* koff, int E, int K,
+                             uint32_t row_bytes, uint32_t* gtab, uint32_t* xtab, int ld, hipStream_t s);
 hipError_t launch_slot_sum(const float* dxs, int T, int K, int d, void* dx, hipStream_t s);
 // Zeroes the windows of experts with no rows in a slab-major operand [ld / 64][C][64].
 hipError_t launch_zero_empty_windows(void* out, int C, const int32_t* offsets, const int32_t* koff, int E,
