@@ -1,61 +1,12 @@
-// Data-movement kernels of the expert-MLP backward: weight transposes, the
-// plan of the weight-gradient products (per-expert K windows cut into work
-// items), its row tables and the sum of their partial blocks, and the per-token
-// sum of the slot gradients. The products themselves run on the MFMA kernels
+// Data-movement kernels of the expert-MLP backward: the plan of the
+// weight-gradient products (per-expert K windows cut into work items), its row
+// tables and the sum of their partial blocks, and the per-token sum of the slot
+// gradients. The products themselves run on the MFMA kernels
 // of gemm.hip and wgrad.hip.
 #include "moe_internal.h"
 
 namespace moe {
 namespace {
-
-// 16-byte store with the non-temporal hint: the transposed operands are read
-// by a later kernel, and keeping their lines in L2 only evicts data still in
-// use (1 % of the backward at ViT-G).
-__device__ __forceinline__ void store16_nt(void* p, const uint4& v) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(p));
-}
-
-constexpr int TT = 64;  // transpose tile (rows x columns)
-
-// out[g][c][r] = in[g][src(r)][c]: the transpose of a [G][Rs][C] bf16 tensor
-// viewed as R rows (R, C multiples of 64). Without padding (ld = 0) src(r) =
-// r and R = Rs. With padding (stacked gate and up rows of h each, ld = h
-// rounded up to 64, R = 2 ld): rows r < ld are gate row r, rows ld + i are up
-// row h + i, and rows past h in either half are zero. One 64 x 64 tile per
-// workgroup through LDS: 16-byte row pieces in, 16-byte pieces of the
-// transposed rows out.
-__global__ __launch_bounds__(256) void k_transpose_w(const bf16_t* __restrict__ in, int Rs, int R, int C, int h,
-                                                    int ld, bf16_t* __restrict__ out) {
-    __shared__ bf16_t tile[TT][TT + 2];
-    const int r0 = blockIdx.x * TT, c0 = blockIdx.y * TT;
-    const size_t g = blockIdx.z;
-    const bf16_t* src = in + g * (size_t)Rs * C;
-    bf16_t* dst = out + g * (size_t)R * C;
-    const int tid = threadIdx.x;
-    for (int q = tid; q < TT * TT / 8; q += 256) {
-        const int r = q / (TT / 8), c = (q % (TT / 8)) * 8;
-        int sr = r0 + r;
-        if (ld > 0) {
-            const int up = sr >= ld, i = sr - (up ? ld : 0);
-            sr = i < h ? i + (up ? h : 0) : -1;
-        }
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (sr >= 0) v = *reinterpret_cast<const uint4*>(src + (size_t)sr * C + c0 + c);
-        const bf16_t* e = reinterpret_cast<const bf16_t*>(&v);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) tile[r][c + k] = e[k];
-    }
-    __syncthreads();
-    for (int q = tid; q < TT * TT / 8; q += 256) {
-        const int c = q / (TT / 8), r = (q % (TT / 8)) * 8;
-        uint4 v;
-        bf16_t* e = reinterpret_cast<bf16_t*>(&v);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) e[k] = tile[r + k][c];
-        store16_nt(dst + (size_t)(c0 + c) * R + r0 + r, v);
-    }
-}
 
 // Plan of the weight-gradient products, one workgroup:
 //  - K windows: expert e owns positions koff[e] .. koff[e+1], its row count
@@ -233,18 +184,6 @@ __global__ __launch_bounds__(256) void k_slot_sum(const float* __restrict__ dxs,
 }
 
 }  // namespace
-
-hipError_t launch_transpose_w(const void* in, int G, int R, int C, void* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_transpose_w, dim3(R / TT, C / TT, G), dim3(256), 0, s, static_cast<const bf16_t*>(in), R, R,
-                       C, 0, 0, static_cast<bf16_t*>(out));
-    return hipGetLastError();
-}
-
-hipError_t launch_transpose_w13(const void* in, int G, int h, int ld, int C, void* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_transpose_w, dim3(2 * ld / TT, C / TT, G), dim3(256), 0, s, static_cast<const bf16_t*>(in),
-                       2 * h, 2 * ld, C, h, ld, static_cast<bf16_t*>(out));
-    return hipGetLastError();
-}
 
 hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
                              int32_t* wcount, hipStream_t s) {

@@ -121,6 +121,12 @@ __host__ __device__ constexpr bool fc1_epi(int epi) {
     return epi == EPI_GELU_STORE || epi == EPI_SWIGLU_STORE || epi == EPI_SWIGLU_BWD;
 }
 
+// Backward products whose weights the bf16 kernels read as they lie in
+// memory, the contraction along their rows.
+__host__ __device__ constexpr bool kmajor_epi(int epi) {
+    return epi == EPI_DGELU || epi == EPI_DSWIGLU || epi == EPI_SCATTER_SLOT_F32;
+}
+
 // Derivative of gelu_sig, so that the backward differentiates the function
 // the forward evaluated: with sg = Sigmoid(s), e = exp(-s), 1 - sg = e sg and
 // d/dx [x sg] = sg (1 + x e sg s'(x)), s'(x) = a0 + 3 a1 x^2 + 5 a2 x^4 (past
@@ -204,10 +210,20 @@ void k_gemm_bf16(const GemmArgs a) {
     static_assert(!SWIGLU || FN % 2 == 0, "SwiGLU waves hold gate and up blocks in pairs");
     const int Kd = a.Kdim;
     const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.A, a.a_bytes);
+    // K-major weights ([Kdim][N]): a slab is 64 rows of WROWB bytes, whose chunks
+    // are swizzled so that a transposing read's 4 rows x 32 columns per half wave
+    // (16 chunks) fall in distinct banks.
+    constexpr bool KM = kmajor_epi(EPI);
+    constexpr int WROWB = BN * 2, WCPR = BN / 8;
+    static_assert(!KM || (BK == 64 && (BN == 64 || BN == 128)), "K-major weight slabs are 64 rows of 64 or 128 columns");
+    auto wswz = [](int r) { return BN == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; };
+    const uint32_t krow = (uint32_t)a.N * 2;
     // SwiGLU: the group's 2 act_n weight rows; reads past them return zeros.
     const __amdgpu_buffer_rsrc_t wres =
-        make_rsrc(static_cast<const bf16_t*>(a.B) + (size_t)tc.e * a.b_group_stride,
-                  (uint32_t)(SWIGLU ? 2 * a.act_n : weight_rows(a)) * Kd * 2);
+        KM ? make_rsrc(static_cast<const bf16_t*>(a.B) + (size_t)tc.e * a.b_group_stride + tc.n0,
+                       (uint32_t)a.b_group_stride * 2u - (uint32_t)tc.n0 * 2u)
+           : make_rsrc(static_cast<const bf16_t*>(a.B) + (size_t)tc.e * a.b_group_stride,
+                       (uint32_t)(SWIGLU ? 2 * a.act_n : weight_rows(a)) * Kd * 2);
 
     constexpr int SWZ_SHIFT = CPR == 8 ? 1 : 2;
     constexpr int SWZ_MASK = CPR - 1;
@@ -240,6 +256,7 @@ void k_gemm_bf16(const GemmArgs a) {
             wrow = tc.n0 / 2 + (r / WTN) * HW + w % HW + (w >= HW ? a.act_n : 0);
         }
         wv[i] = (uint32_t)wrow * rstride + c * 16;
+        if (KM) wv[i] = (uint32_t)(sl / WCPR) * krow + (uint32_t)((sl % WCPR) ^ wswz(sl / WCPR)) * 16u;
     }
 
     f32x16_t acc[FN][FM];
@@ -256,13 +273,19 @@ void k_gemm_bf16(const GemmArgs a) {
     const int fr = lane & 31;
     const int fk = lane >> 5;
     const int lane_sw = (fr >> SWZ_SHIFT) & SWZ_MASK;
-    uint32_t xoff[KS], woff[KS];
+    uint32_t xoff[KS], woff[KS], wkoff[FN];
     const uint32_t base = lds_address(smem);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         const uint32_t k = fr * ROWB + (((ks * 2 + fk) ^ lane_sw) << 4);
         xoff[ks] = base + (wm * WTM) * ROWB + k;
         woff[ks] = base + BM * ROWB + (wn * WTN) * ROWB + k;
+    }
+    const int r4 = (lane & 15) >> 2;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {  // K-major weights: by 32-column block
+        const int c = wn * (WTN / 8) + j * 4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+        wkoff[j] = base + BM * ROWB + (uint32_t)(fk * 8 + r4) * WROWB + (uint32_t)(c ^ wswz(r4)) * 16u + (lane & 1) * 8u;
     }
     // K range: the whole row, or (split K, dense fp32 output) part blockIdx.y of
     // gridDim.y equal parts.
@@ -280,6 +303,18 @@ void k_gemm_bf16(const GemmArgs a) {
         for (int i = 0; i < AP; ++i) copy16_to_lds(xres, xv[i], soff, buf + (wave + NW * i) * 1024);
 #pragma unroll
         for (int i = 0; i < BP; ++i) {
+            if constexpr (KM) {
+                // Stacked weights (a.b_half > 0), as in k_gemm_pp.
+                const int half = EPI == EPI_SCATTER_SLOT_F32 ? a.b_half : 0;
+                const int up = half > 0 && kslab * BK >= half ? 1 : 0;
+                const int kk = kslab * BK - up * half;
+                uint32_t v = wv[i] + (uint32_t)(kk + (up ? a.act_n : 0)) * krow;
+                if (half > 0 && ((wave + NW * i) * kWave + lane) / WCPR + kk >= a.act_n) v = kWgradNoRow;
+                uint8_t* const dst = buf + BM * ROWB + (wave + NW * i) * 1024;
+                if (a.b_nt) copy16_to_lds_nt(wres, v, 0, dst);
+                else copy16_to_lds(wres, v, 0, dst);
+                continue;
+            }
             // Weights read once in this launch (a.b_nt: one M-tile per expert
             // on average) stream past the caches.
             if (a.b_nt)
@@ -288,24 +323,41 @@ void k_gemm_bf16(const GemmArgs a) {
                 copy16_to_lds(wres, wv[i], soff, buf + BM * ROWB + (wave + NW * i) * 1024);
         }
     };
-    auto read_frags = [&](uint32_t sbase, int ks, bf16x8_t* xf, bf16x8_t* wf) {
+    auto read_frags = [&](uint32_t sbase, auto KSC, bf16x8_t* xf, bf16x8_t* wf, u32x2_t (*wh)[2]) {
+        constexpr int ks = decltype(KSC)::value;
         const uint32_t xa = xoff[ks] + sbase, wa = woff[ks] + sbase;
         if constexpr (FM >= 1) xf[0] = lds_read16<0 * 32 * ROWB>(xa);
         if constexpr (FM >= 2) xf[1] = lds_read16<1 * 32 * ROWB>(xa);
         if constexpr (FM >= 3) xf[2] = lds_read16<2 * 32 * ROWB>(xa);
         if constexpr (FM >= 4) xf[3] = lds_read16<3 * 32 * ROWB>(xa);
+        if constexpr (KM) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                lds_read_tr8_asm<ks * 16 * WROWB>(wh[j][0], wkoff[j] + sbase);
+                lds_read_tr8_asm<ks * 16 * WROWB + 4 * WROWB>(wh[j][1], wkoff[j] + sbase);
+            }
+            return;
+        }
         if constexpr (FN >= 1) wf[0] = lds_read16<0 * 32 * ROWB>(wa);
         if constexpr (FN >= 2) wf[1] = lds_read16<1 * 32 * ROWB>(wa);
         if constexpr (FN >= 3) wf[2] = lds_read16<2 * 32 * ROWB>(wa);
         if constexpr (FN >= 4) wf[3] = lds_read16<3 * 32 * ROWB>(wa);
         static_assert(FM <= 4 && FN <= 4, "at most 4x4 blocks per wave");
     };
-    auto settle = [&](bf16x8_t* xf, bf16x8_t* wf) {
+    auto settle = [&](bf16x8_t* xf, bf16x8_t* wf, u32x2_t (*wh)[2]) {
         wait_lgkmcnt0();
 #pragma unroll
         for (int i = 0; i < FM; ++i) tie(xf[i]);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) tie(wf[j]);
+        for (int j = 0; j < FN; ++j) {
+            if constexpr (KM) {
+                tie(wh[j][0]);
+                tie(wh[j][1]);
+                wf[j] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(wh[j][0], wh[j][1], 0, 1, 2, 3));
+            } else {
+                tie(wf[j]);
+            }
+        }
     };
 
 #pragma unroll
@@ -328,20 +380,21 @@ void k_gemm_bf16(const GemmArgs a) {
         }
         const uint32_t sbase = cur_stage * STAGE;
         bf16x8_t xf[2][FM], wf[2][FN];
-        read_frags(sbase, 0, xf[0], wf[0]);
-        settle(xf[0], wf[0]);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int c = ks & 1;
-            if (ks + 1 < KS) read_frags(sbase, ks + 1, xf[c ^ 1], wf[c ^ 1]);
+        u32x2_t wh[2][FN][2];  // K-major weights: the two row halves of each fragment
+        read_frags(sbase, std::integral_constant<int, 0>{}, xf[0], wf[0], wh[0]);
+        settle(xf[0], wf[0], wh[0]);
+        static_for<KS>([&](auto KSC) {
+            constexpr int ks = decltype(KSC)::value, c = ks & 1;
+            if constexpr (ks + 1 < KS)
+                read_frags(sbase, std::integral_constant<int, ks + 1>{}, xf[c ^ 1], wf[c ^ 1], wh[c ^ 1]);
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
                     acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c][j], xf[c][i], acc[j][i], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if (ks + 1 < KS) settle(xf[c ^ 1], wf[c ^ 1]);
-        }
+            if constexpr (ks + 1 < KS) settle(xf[c ^ 1], wf[c ^ 1], wh[c ^ 1]);
+        });
         if (++cur_stage == STAGES) cur_stage = 0;
     }
 
@@ -854,6 +907,7 @@ void k_gemm_pp(const GemmArgs a) {
     constexpr bool SWIGLU = EPI == EPI_SWIGLU_STORE || EPI == EPI_SWIGLU_BWD;
     constexpr bool SWBWD = EPI == EPI_SWIGLU_BWD;  // and the fp32 gate / up pre-activations into C2
     constexpr bool SCATTER = EPI == EPI_SCATTER_SLOT || EPI == EPI_SCATTER_SLOT_F32;
+    constexpr bool KM = kmajor_epi(EPI);  // weights [Kdim][N]: fragments by transposing reads
     constexpr bool RNORM = EPI == EPI_ROUTER_F32;  // EPI_STORE_F32 and the token rows' sums of squares
     constexpr bool OUT_F32 = EPI == EPI_STORE_F32 || EPI == EPI_SCATTER_SLOT_F32 || RNORM;
     constexpr bool COMBINE = EPI == EPI_COMBINE;
@@ -937,6 +991,8 @@ void k_gemm_pp(const GemmArgs a) {
         if (SWIGLU)
             return make_rsrc(Bw + (size_t)t.e * a.b_group_stride + (size_t)(t.n0 / 2) * Kd,
                              (uint32_t)__builtin_amdgcn_readfirstlane(2 * a.act_n - t.n0 / 2) * rowbytes);
+        if (KM)  // every weight row of the expert, columns from n0
+            return make_rsrc(Bw + (size_t)t.e * a.b_group_stride + t.n0, (uint32_t)a.b_group_stride * 2u - (uint32_t)t.n0 * 2u);
         const int rows = __builtin_amdgcn_readfirstlane(max(0, min(BN, weight_rows(a) - t.n0)));
         return make_rsrc(Bw + (size_t)t.e * a.b_group_stride + (size_t)t.n0 * Kd, (uint32_t)rows * rowbytes);
     };
@@ -972,6 +1028,15 @@ void k_gemm_pp(const GemmArgs a) {
         wv[i] = (uint32_t)wrow * rowbytes + c * 16;
         tv[i] = (uint32_t)r * rowbytes + c * 16;
     }
+    // K-major weights: LDS rows of 512 bytes, 16-byte chunk c of row r at chunk
+    // c ^ ((r & 3) << 2) (a transposing read takes 4 rows x 32 columns per half
+    // wave, 16 chunks in distinct banks); piece p of a wave is rows 16 w + 2 p
+    // and the next.
+    const int hb = lane >> 5;
+    const uint32_t krow = (uint32_t)ncols * 2;
+    const uint32_t klane = 16 * wave + hb;
+    const uint32_t kbase[2] = {klane * krow + (uint32_t)((lane & 31) ^ (hb << 2)) * 16u,
+                               klane * krow + (uint32_t)((lane & 31) ^ ((2 + hb) << 2)) * 16u};
     // Gathered token rows: slot -> token, rows past the tile's end repeat its last row.
     auto load_tokens = [&](const Tile& t, int32_t (&tok)[AP]) {
 #pragma unroll
@@ -1043,22 +1108,53 @@ void k_gemm_pp(const GemmArgs a) {
         const uint32_t k = fr * ROWB + (((ks * 2 + fk) ^ lane_sw) << 4);
         xoff[ks] = base + (wm * WT) * ROWB + k;
         woff[ks] = base + WBASE + (wn * WT) * ROWB + k;
+        if constexpr (KM) {  // by 32-column block instead of by K step
+            const int r4 = (lane & 15) >> 2;
+            woff[ks] = base + WBASE + (uint32_t)(fk * 8 + r4) * 512u + (uint32_t)(lane & 1) * 8u +
+                       (uint32_t)(wn * 16 + ((ks ^ r4) << 2) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16u;
+        }
     }
 
     auto copy_a = [&](auto LC, int stage, uint32_t soff, __amdgpu_buffer_rsrc_t xr, const uint32_t (&xv)[AP]) {
         constexpr int L = decltype(LC)::value;
         copy16_to_lds(xr, xv[L], soff, smem + stage * SLAB + (wave + NW * L) * 1024);
     };
-    auto copy_w = [&](auto LC, int stage, uint32_t soff, __amdgpu_buffer_rsrc_t wr) {
+    auto copy_w = [&](auto LC, int stage, int slab, __amdgpu_buffer_rsrc_t wr) {
         constexpr int L = decltype(LC)::value;
-        copy16_to_lds(wr, wv[L], soff, smem + WBASE + stage * SLAB + (wave + NW * L) * 1024);
+        if constexpr (KM) {
+            // Stacked weights (a.b_half > 0): K columns b_half .. are the second
+            // matrix's rows, act_n rows after the first's; K columns past act_n in
+            // either half have no weight row and read as zeros.
+            const int half = EPI == EPI_SCATTER_SLOT_F32 ? a.b_half : 0;
+            const int up = half > 0 && slab * BK >= half ? 1 : 0;
+            const int kk = slab * BK - up * half;
+            uint32_t v = kbase[L & 1] + (uint32_t)(kk + (up ? a.act_n : 0) + 2 * L) * krow;
+            if (half > 0 && (int)klane + 2 * L + kk >= a.act_n) v = kWgradNoRow;
+            copy16_to_lds(wr, v, 0, smem + WBASE + stage * SLAB + (wave * 8 + L) * 1024);
+        } else {
+            copy16_to_lds(wr, wv[L], soff_of(slab), smem + WBASE + stage * SLAB + (wave + NW * L) * 1024);
+        }
     };
 
     bf16x8_t xf[2][FB], wf[2][FB];
-    auto read_frag = [&](auto NBC, auto QC, uint32_t abase, uint32_t wbase, int ks) {
-        constexpr int nb = decltype(NBC)::value, q = decltype(QC)::value;
-        if constexpr (q < FB) xf[nb][q] = lds_read16<q * 32 * ROWB>(xoff[ks] + abase);
-        else wf[nb][q - FB] = lds_read16<(q - FB) * 32 * ROWB>(woff[ks] + wbase);
+    u32x2_t wh[2][FB][2];  // K-major weights: the two row halves of each fragment
+    auto read_frag = [&](auto NBC, auto QC, uint32_t abase, uint32_t wbase, auto KSC) {
+        constexpr int nb = decltype(NBC)::value, q = decltype(QC)::value, ks = decltype(KSC)::value;
+        if constexpr (q < FB) {
+            xf[nb][q] = lds_read16<q * 32 * ROWB>(xoff[ks] + abase);
+        } else if constexpr (KM) {
+            lds_read_tr8_asm<ks * 16 * 512>(wh[nb][q - FB][0], woff[q - FB] + wbase);
+            lds_read_tr8_asm<ks * 16 * 512 + 4 * 512>(wh[nb][q - FB][1], woff[q - FB] + wbase);
+        } else {
+            wf[nb][q - FB] = lds_read16<(q - FB) * 32 * ROWB>(woff[ks] + wbase);
+        }
+    };
+    auto wfrag = [&](auto CBC, auto JC) {
+        constexpr int cb = decltype(CBC)::value, j = decltype(JC)::value;
+        if constexpr (KM)
+            return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(wh[cb][j][0], wh[cb][j][1], 0, 1, 2, 3));
+        else
+            return wf[cb][j];
     };
     auto settle = [&](auto CBC) {
         constexpr int cb = decltype(CBC)::value;
@@ -1066,7 +1162,14 @@ void k_gemm_pp(const GemmArgs a) {
 #pragma unroll
         for (int i = 0; i < FB; ++i) tie(xf[cb][i]);
 #pragma unroll
-        for (int j = 0; j < FB; ++j) tie(wf[cb][j]);
+        for (int j = 0; j < FB; ++j) {
+            if constexpr (KM) {
+                tie(wh[cb][j][0]);
+                tie(wh[cb][j][1]);
+            } else {
+                tie(wf[cb][j]);
+            }
+        }
     };
     // Router logits: per lane, the sums of squares of its four token rows'
     // values in the token fragments (lanes l and l + 32 hold the two halves
@@ -1079,12 +1182,13 @@ void k_gemm_pp(const GemmArgs a) {
     // MFMA q (q < 8), copy q / 4 of the step's four after MFMA q when q % 4 == 1.
     // Router logits: after MFMA q, the squares of the two values in 32-bit
     // word q % 4 of token fragment q / 4 (VALU work beside the MFMAs).
-    auto kstep = [&](auto CBC, uint32_t rabase, uint32_t rwbase, int rks, auto&& copy) {
+    auto kstep = [&](auto CBC, uint32_t rabase, uint32_t rwbase, auto KSC, auto&& copy) {
         constexpr int cb = decltype(CBC)::value;
         static_for<FB * FB>([&](auto QC) {
             constexpr int q = decltype(QC)::value;
             constexpr int j = q / FB, i = q % FB;
-            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cb][j], xf[cb][i], acc[j][i], 0, 0, 0);
+            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfrag(CBC, std::integral_constant<int, j>{}), xf[cb][i],
+                                                                acc[j][i], 0, 0, 0);
             if constexpr (RNORM) {
                 const uint32_t u = __builtin_bit_cast(u32x4_t, xf[cb][q / 4])[q % 4];
                 const float lo = __uint_as_float(u << 16), hi = __uint_as_float(u & 0xffff0000u);
@@ -1092,7 +1196,7 @@ void k_gemm_pp(const GemmArgs a) {
                 xsq[q / 4] = fmaf(hi, hi, xsq[q / 4]);
             }
             if constexpr (q < 2 * FB)
-                read_frag(std::integral_constant<int, cb ^ 1>{}, QC, rabase, rwbase, rks);
+                read_frag(std::integral_constant<int, cb ^ 1>{}, QC, rabase, rwbase, KSC);
             if constexpr (q % 4 == 1) copy(std::integral_constant<int, q / 4>{});
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -1279,13 +1383,17 @@ void k_gemm_pp(const GemmArgs a) {
                     float4 fac[FB][4];
                     if constexpr (DG) {
                         const int r = wm * WT + i * 32 + fr;
+                        // Columns past the width (N rounded up) re-read its first and are not stored.
                         const float* arow = static_cast<const float*>(a.aux) +
-                                            (size_t)(t.row0 + min(r, t.rows - 1)) * a.N + t.n0 + wn * WT + 4 * fk;
+                                            (size_t)(t.row0 + min(r, t.rows - 1)) * ncols + 4 * fk;
 #pragma unroll
                         for (int j = 0; j < FB; ++j)
 #pragma unroll
                             for (int g = 0; g < 4; ++g)
-                                fac[j][g] = *reinterpret_cast<const float4*>(arow + j * 32 + 8 * g);
+                                {
+                                const int c = t.n0 + wn * WT + j * 32;
+                                fac[j][g] = *reinterpret_cast<const float4*>(arow + (c < ncols ? c : 0) + 8 * g);
+                            }
                     }
 #pragma unroll
                     for (int j = 0; j < FB; ++j)
@@ -1347,7 +1455,7 @@ void k_gemm_pp(const GemmArgs a) {
                     // DSW: pieces 0..7 of the row are dG, 8..15 dU (act_ld further on).
                     const int pcol = DSW ? (lane & 7) * 8 : (lane & 15) * (16 / OES);
                     const int col = t.n0 + wn * WT + h * 64 + pcol;
-                    if (r < t.rows && t.n0 + wn * WT + h * 64 < ncols && (!DSW || col < a.act_ld)) {
+                    if (r < t.rows && (KM || BWD1 ? col : t.n0 + wn * WT + h * 64) < ncols) {
                         const size_t orw = SCATTER ? (size_t)orow[i][k] : (size_t)(t.row0 + r);
                         uint8_t* out = cbase + (orw * ostr + t.n0 + wn * WT + h * 64) * OES + (lane & 15) * 16;
                         if (DSW) out = cbase + (orw * ostr + ((lane & 8) ? a.act_ld : 0) + col) * 2;
@@ -1425,9 +1533,9 @@ void k_gemm_pp(const GemmArgs a) {
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         const int r = wm * WT + i * 32 + (lane >> 4) + 4 * k;
-                        if (r < t.rows)
+                        if (r < t.rows && t.n0 + wn * WT + h * 64 < ncols)
                             store16_asm(static_cast<uint8_t*>(a.C2) +
-                                            ((size_t)(t.row0 + r) * a.N + t.n0 + wn * WT + h * 64) * 4 + (lane & 15) * 16,
+                                            ((size_t)(t.row0 + r) * ncols + t.n0 + wn * WT + h * 64) * 4 + (lane & 15) * 16,
                                         v[k]);
                     }
                 }
@@ -1438,12 +1546,12 @@ void k_gemm_pp(const GemmArgs a) {
     // Prologue: token slab 0, weight slab 0, token slab 1, the first half of
     // weight slab 1; wait for slab 0 of both operands; read its first fragments.
     static_for<AP>([&](auto LC) { copy_a(LC, 0, soff_of(0), xres_c, GATHER ? xv_c : tv); });
-    static_for<BP>([&](auto LC) { copy_w(LC, 0, soff_of(0), wres_c); });
+    static_for<BP>([&](auto LC) { copy_w(LC, 0, 0, wres_c); });
     static_for<AP>([&](auto LC) { copy_a(LC, 1, soff_of(1), xres_c, GATHER ? xv_c : tv); });
-    static_for<BP / 2>([&](auto LC) { copy_w(LC, 1, soff_of(1), wres_c); });
+    static_for<BP / 2>([&](auto LC) { copy_w(LC, 1, 1, wres_c); });
     wait_vmcnt<AP + BP / 2>();
     barrier_no_fence();
-    static_for<2 * FB>([&](auto QC) { read_frag(std::integral_constant<int, 0>{}, QC, 0u, 0u, 0); });
+    static_for<2 * FB>([&](auto QC) { read_frag(std::integral_constant<int, 0>{}, QC, 0u, 0u, std::integral_constant<int, 0>{}); });
 
     int as = 0, ws = 0;  // ring slots of the slab being multiplied
     for (;;) {
@@ -1454,8 +1562,8 @@ void k_gemm_pp(const GemmArgs a) {
             const int ws1 = ws ^ 1;
             // Slabs kt + 1 and kt + 2 may belong to the next tile.
             const bool n1 = kt + 1 >= nk, n2 = kt + 2 >= nk;
-            const uint32_t so1 = soff_of(n1 ? kt + 1 - nk : kt + 1);
-            const uint32_t so2 = soff_of(n2 ? kt + 2 - nk : kt + 2);
+            const int s1 = n1 ? kt + 1 - nk : kt + 1, s2 = n2 ? kt + 2 - nk : kt + 2;
+            const uint32_t so2 = soff_of(s2);
             const __amdgpu_buffer_rsrc_t wr1 = n1 ? wres_n : wres_c;
             const __amdgpu_buffer_rsrc_t xr2 = n2 ? xres_n : xres_c;
             const __amdgpu_buffer_rsrc_t wr2 = n2 ? wres_n : wres_c;
@@ -1464,16 +1572,16 @@ void k_gemm_pp(const GemmArgs a) {
             for (int i = 0; i < AP; ++i) xv2[i] = GATHER ? (n2 ? xv_n[i] : xv_c[i]) : tv[i];
             // K step 0: second half of weight slab kt + 1.
             settle(std::integral_constant<int, 0>{});
-            kstep(std::integral_constant<int, 0>{}, abase, wbase, 1, [&](auto CC) {
-                copy_w(std::integral_constant<int, BP / 2 + decltype(CC)::value>{}, ws1, so1, wr1);
+            kstep(std::integral_constant<int, 0>{}, abase, wbase, std::integral_constant<int, 1>{}, [&](auto CC) {
+                copy_w(std::integral_constant<int, BP / 2 + decltype(CC)::value>{}, ws1, s1, wr1);
             });
             // K steps 1 and 2: token slab kt + 2.
             settle(std::integral_constant<int, 1>{});
-            kstep(std::integral_constant<int, 1>{}, abase, wbase, 2, [&](auto CC) {
+            kstep(std::integral_constant<int, 1>{}, abase, wbase, std::integral_constant<int, 2>{}, [&](auto CC) {
                 copy_a(std::integral_constant<int, decltype(CC)::value>{}, as2, so2, xr2, xv2);
             });
             settle(std::integral_constant<int, 0>{});
-            kstep(std::integral_constant<int, 0>{}, abase, wbase, 3, [&](auto CC) {
+            kstep(std::integral_constant<int, 0>{}, abase, wbase, std::integral_constant<int, 3>{}, [&](auto CC) {
                 copy_a(std::integral_constant<int, 4 + decltype(CC)::value>{}, as2, so2, xr2, xv2);
             });
             settle(std::integral_constant<int, 1>{});
@@ -1484,9 +1592,10 @@ void k_gemm_pp(const GemmArgs a) {
             barrier_no_fence();
             // K step 3: first fragments of slab kt + 1; first half of weight
             // slab kt + 2 into the weight slot of slab kt.
-            kstep(std::integral_constant<int, 1>{}, (uint32_t)as1 * SLAB, (uint32_t)ws1 * SLAB, 0, [&](auto CC) {
-                copy_w(std::integral_constant<int, decltype(CC)::value>{}, ws, so2, wr2);
-            });
+            kstep(std::integral_constant<int, 1>{}, (uint32_t)as1 * SLAB, (uint32_t)ws1 * SLAB,
+                  std::integral_constant<int, 0>{}, [&](auto CC) {
+                      copy_w(std::integral_constant<int, decltype(CC)::value>{}, ws, s2, wr2);
+                  });
             as = as1;
             ws = ws1;
         } while (++kt < nk);
@@ -1547,7 +1656,8 @@ void k_gemm_pp(const GemmArgs a) {
         // copies refill that slot.
         barrier_no_fence();
         static_for<2 * FB>([&](auto QC) {
-            read_frag(std::integral_constant<int, 0>{}, QC, (uint32_t)as * SLAB, (uint32_t)ws * SLAB, 0);
+            read_frag(std::integral_constant<int, 0>{}, QC, (uint32_t)as * SLAB, (uint32_t)ws * SLAB,
+                      std::integral_constant<int, 0>{});
         });
     }
     wait_vmcnt<0>();
@@ -1800,23 +1910,26 @@ hipError_t dispatch_bf16(int bm, const GemmArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-// Backward products: the persistent kernel on 256-row tiles where the widths
-// allow (rounded up to the tile for SwiGLU dA and the weight gradients), else
-// the tiled kernel with 256- or 64-row tiles.
+bool gemm_backward_pp(int bm, int epilogue, int n, int kdim) {
+    // SwiGLU dA at any width, as the recompute before it; the others where
+    // rounding N up to the 256-column tile adds at most a third.
+    const int n256 = (n + 255) / 256 * 256;
+    return bm == 256 && kdim >= 128 && (epilogue == EPI_DSWIGLU || n256 * 3 <= n * 4);
+}
+
+// Backward products: the persistent kernel where gemm_backward_pp says so, N
+// rounded up to the tile (weights past N read as zeros or as other weights and
+// feed columns that are not stored), else the tiled kernel with 256- or 64-row
+// tiles.
 template <int EPI, bool GROUPED>
 hipError_t dispatch_tiled(int bm, const GemmArgs& a, hipStream_t s) {
-    constexpr bool ROW_PRODUCT = EPI == EPI_GELU_BWD || EPI == EPI_DGELU || EPI == EPI_SCATTER_SLOT_F32;
-    if constexpr (ROW_PRODUCT)
-        if (bm == 256 && a.N % 256 == 0 && a.Kdim >= 128) return launch_pp<EPI, GROUPED>(a, s);
-    // SwiGLU dA: N = act_ld rounded up to the tile width; W2's transposed rows
-    // past act_ld read as zeros and those columns are not stored.
-    if constexpr (EPI == EPI_DSWIGLU)
-        if (bm == 256 && a.Kdim >= 128) {
-            GemmArgs p = a;
-            p.b_rows = a.act_ld;
-            p.N = (a.act_ld + 255) / 256 * 256;
-            return launch_pp<EPI, GROUPED>(p, s);
-        }
+    if (gemm_backward_pp(bm, EPI, a.N, a.Kdim)) {
+        GemmArgs p = a;
+        p.b_rows = a.N;
+        p.ldc = a.N;
+        p.N = (a.N + 255) / 256 * 256;
+        return launch_pp<EPI, GROUPED>(p, s);
+    }
     if (bm == 256) {
         if (a.N % 128 == 0) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI, GROUPED>(a, s);
         return launch_bf16<256, 64, 4, 1, 64, 2, 1, EPI, GROUPED>(a, s);

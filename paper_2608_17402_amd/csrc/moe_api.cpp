@@ -237,10 +237,8 @@ BackwardPlan plan_backward(const moe_desc_t& d) {
     const bool sw = d.flags & MOE_FLAG_SWIGLU;
     b.hh = act_stride(d, d.h);
     b.hw = sw ? 2 * b.hh : b.hh;
-    const size_t hh = b.hh, hw = b.hw;
+    const size_t hw = b.hw;
     b.pre = take(TK * hw * 4);
-    b.w1t = take((size_t)d.E * d.d * hw * 2);
-    b.w2t = take((size_t)d.E * hh * d.d * 2);
     b.dh = take(TK * hw * 2);
     b.dxs = take(TK * d.d * 4);
     b.koff = take(((size_t)d.E + 1) * 4);
@@ -416,8 +414,6 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     int32_t* ntiles = region<int32_t>(ws, p.ntiles);
     void* act = region<void>(ws, p.act);
     float* pre = region<float>(ws, b.pre);
-    void* w1t = region<void>(ws, b.w1t);
-    void* w2t = region<void>(ws, b.w2t);
     void* dh = region<void>(ws, b.dh);
     float* dxs = region<float>(ws, b.dxs);
     int32_t* koff = region<int32_t>(ws, b.koff);
@@ -431,9 +427,6 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     HIP_CHECK(launch_wgrad_plan(offsets, d.E, koff, items, rlist, wcount, s), "weight-gradient plan");
     HIP_CHECK(launch_wgrad_rows(sorted_slots, offsets, koff, d.E, d.K, (uint32_t)d.d * 2, gtab, xtab, b.ld, s),
               "weight-gradient rows");
-    if (sw) HIP_CHECK(launch_transpose_w13(w1, d.E, d.h, hh, d.d, w1t, s), "transpose w13");
-    else HIP_CHECK(launch_transpose_w(w1, d.E, d.h, d.d, w1t, s), "transpose w1");
-    HIP_CHECK(launch_transpose_w(w2, d.E, d.d, hh, w2t, s), "transpose w2");
 
     GemmArgs g{};  // fc1 again: the activation (bf16) and the pre-activations (fp32)
     g.A = x;
@@ -456,7 +449,7 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
 
     GemmArgs ga = g;  // dH from Gout W2 and the pre-activations
     ga.A = gout;
-    ga.B = w2t;
+    ga.B = w2;
     ga.C = dh;
     ga.C2 = nullptr;
     ga.aux = pre;
@@ -468,12 +461,13 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
 
     GemmArgs gx = g;  // slot gradients of x: dH W1, fp32 to slot order
     gx.A = dh;
-    gx.B = w1t;
+    gx.B = w1;
     gx.C = dxs;
     gx.C2 = nullptr;
     gx.N = d.d;
     gx.Kdim = hw;
-    gx.b_group_stride = (int64_t)d.d * hw;
+    gx.b_group_stride = (int64_t)(sw ? 2 : 1) * d.h * d.d;
+    gx.b_half = sw ? hh : 0;
     gx.row_mode = ROWS_IDENTITY;
     gx.a_bytes = (uint32_t)(TK * hw * 2);
     HIP_CHECK(launch_gemm(d, EPI_SCATTER_SLOT_F32, p.tile_bm, gx, s), "backward dx");

@@ -68,7 +68,8 @@ enum GemmEpilogue : int {
 
 struct GemmArgs {
     const void* A;             // rows of length Kdim (layer dtype)
-    const void* B;             // weights [groups][N][Kdim] (layer dtype)
+    const void* B;             // weights [groups][N][Kdim] (layer dtype); EPI_DGELU, EPI_DSWIGLU and
+                               // EPI_SCATTER_SLOT_F32: [groups][Kdim][N]
     void* C;                   // output rows of length N
     const int32_t* row_map;    // sorted_slots (gather / scatter), may be null for identity
     const TileDesc* tiles;     // grouped mode: tile table
@@ -86,6 +87,8 @@ struct GemmArgs {
     const void* aux;           // EPI_DGELU: the pre-activation (fp32, rows of N); EPI_DSWIGLU: G, U
     int32_t ldc;               // persistent kernel, EPI_DSWIGLU: the real column count when N
                                // is rounded up to the tile width (0 = N); columns past it are not stored
+    int32_t b_half;            // K-major weights of two stacked matrices: K columns of each half (act_n of them
+                               // with a weight row); 0 = one matrix
     int32_t act_n;             // EPI_SWIGLU_STORE: activation width h (valid columns)
     int32_t act_ld;            // EPI_SWIGLU_STORE: activation row stride (h rounded up to 128)
     const float* gate;         // EPI_COMBINE: gates [rows, route_k]
@@ -122,7 +125,6 @@ struct BackwardPlan {
     // hh = activation row stride (h, or ldh for SwiGLU); hw = pre-activation
     // width (hh, or 2 ldh for SwiGLU: gate columns then up columns).
     size_t pre;              // pre-activations [T*K, hw] fp32, sorted order
-    size_t w1t, w2t;         // transposed weights [E, d, hw] and [E, hh, d]
     size_t dh;               // pre-activation gradient [T*K, hw] bf16, sorted order
     size_t dxs;              // slot gradients of x [T*K, d] fp32, slot order
     size_t koff;             // [E + 1] K-window starts
@@ -184,9 +186,6 @@ hipError_t launch_gemm(const moe_desc_t& d, int epilogue, int bm, const GemmArgs
 // Whether launch_gemm(EPI_COMBINE) supports this dense GEMM (M-tile bm, N columns, K = kdim).
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim);
 // Backward data movement (backward.hip).
-hipError_t launch_transpose_w(const void* in, int G, int R, int C, void* out, hipStream_t s);
-// Stacked gate/up weights [G][2h][C] -> [G][C][2 ld], rows padded to ld each.
-hipError_t launch_transpose_w13(const void* in, int G, int h, int ld, int C, void* out, hipStream_t s);
 // Longest K window of one weight-gradient work item, in 64-column slabs.
 constexpr int kWgradSlabs = 128;
 // One work item of the weight-gradient products: klen window positions from
