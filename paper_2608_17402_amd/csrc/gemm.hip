@@ -368,6 +368,7 @@ void k_gemm_bf16(const GemmArgs a) {
     for (int kt = 0; kt < nk; ++kt) {
         // Slab kt must have landed; later prefetched slabs stay in flight.
         const int ahead = min(nk - 1 - kt, STAGES - 2);
+        if constexpr (STAGES >= 5) { if (ahead >= 3) { wait_vmcnt<3 * (AP + BP)>(); goto waited; } }
         if constexpr (STAGES >= 4) { if (ahead >= 2) { wait_vmcnt<2 * (AP + BP)>(); goto waited; } }
         if constexpr (STAGES >= 3) { if (ahead >= 1) { wait_vmcnt<AP + BP>(); goto waited; } }
         wait_vmcnt<0>();
@@ -1873,6 +1874,26 @@ hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Small launches, where every 64 x 64 tile is resident at once and a workgroup's
+// chain of K slabs, a memory latency apart, is the time: 64 x 64 tiles (more
+// workgroups) with a ring as deep as the residency allows, five slabs at one
+// workgroup per CU, four at two. 0 for larger launches. ViT-L widths, 5 tokens:
+// routed first layer 11.8 -> 9.8 us, shared layers 10.8 -> 8.8 and 9.9 -> 8.2 us
+// against 64 x 128 tiles with three slabs; the layer 61.0 -> 56.6 us.
+int small_ring(const GemmArgs& a) {
+    const long long wgs = (long long)a.max_tiles * (a.N / 64), cus = persistent_grid(1 << 20);
+    if (a.k_splits > 1 || wgs > 2 * cus) return 0;
+    return wgs <= cus ? 5 : 4;
+}
+template <int EPI, bool GROUPED>
+hipError_t launch_64(const GemmArgs& a, hipStream_t s) {
+    const int ring = small_ring(a);
+    if (ring == 5) return launch_bf16<64, 64, 2, 2, 64, 5, 1, EPI, GROUPED>(a, s);
+    if (ring == 4) return launch_bf16<64, 64, 2, 2, 64, 4, 2, EPI, GROUPED>(a, s);
+    if (a.N % 128 == 0) return launch_bf16<64, 128, 1, 4, 64, 3, 2, EPI, GROUPED>(a, s);
+    return launch_bf16<64, 64, 2, 2, 64, 3, 2, EPI, GROUPED>(a, s);
+}
+
 // Tile shapes. Large groups (M-tiles of 256 token rows): 256 x 256 on the
 // persistent kernel when N allows and K spans at least two slabs (the paced
 // one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Small
@@ -1903,10 +1924,7 @@ hipError_t dispatch_bf16(int bm, const GemmArgs& a, hipStream_t s) {
         if (a.N % 128 == 0) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI, GROUPED>(a, s);
         return launch_bf16<256, 64, 4, 1, 64, 2, 1, EPI, GROUPED>(a, s);
     }
-    if (bm == 64) {
-        if (a.N % 128 == 0) return launch_bf16<64, 128, 1, 4, 64, 3, 2, EPI, GROUPED>(a, s);
-        return launch_bf16<64, 64, 2, 2, 64, 3, 2, EPI, GROUPED>(a, s);
-    }
+    if (bm == 64) return launch_64<EPI, GROUPED>(a, s);
     return hipErrorInvalidValue;
 }
 
@@ -1953,6 +1971,8 @@ hipError_t dispatch_swiglu(int bm, GemmArgs a, hipStream_t s) {
     }
     if (bm == 64) {
         a.N = 2 * a.act_ld;
+        if ((long long)a.max_tiles * (a.N / 128) <= persistent_grid(1 << 20))  // as small_ring, one workgroup per CU
+            return launch_bf16<64, 128, 2, 2, 64, 5, 1, EPI_SWIGLU_STORE, GROUPED>(a, s);
         return launch_bf16<64, 128, 2, 2, 64, 3, 2, EPI_SWIGLU_STORE, GROUPED>(a, s);
     }
     return hipErrorInvalidValue;
@@ -2008,8 +2028,7 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
                 if (!GROUPED && gemm_combine_fusable(d, bm, a.N, a.Kdim) && a.route_k == d.K)
                 {
                     if (bm == 256) return launch_pp_combine(a, s);
-                    if (a.N % 128 == 0) return launch_bf16<64, 128, 1, 4, 64, 3, 2, EPI_COMBINE, false>(a, s);
-                    return launch_bf16<64, 64, 2, 2, 64, 3, 2, EPI_COMBINE, false>(a, s);
+                    return launch_64<EPI_COMBINE, false>(a, s);
                 }
                 break;
         }
