@@ -1894,6 +1894,14 @@ hipError_t launch_64(const GemmArgs& a, hipStream_t s) {
     return launch_bf16<64, 64, 2, 2, 64, 3, 2, EPI, GROUPED>(a, s);
 }
 
+// 128-row tiles: 128 x 128 (four waves of 64 x 64, two slabs in the ring, two
+// workgroups per CU) or 128 x 64.
+template <int EPI, bool GROUPED>
+hipError_t launch_128(const GemmArgs& a, hipStream_t s) {
+    if (a.N % 128 == 0) return launch_bf16<128, 128, 2, 2, 64, 2, 2, EPI, GROUPED>(a, s);
+    return launch_bf16<128, 64, 2, 2, 64, 3, 2, EPI, GROUPED>(a, s);
+}
+
 // Tile shapes. Large groups (M-tiles of 256 token rows): 256 x 256 on the
 // persistent kernel when N allows and K spans at least two slabs (the paced
 // one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Small
@@ -1924,6 +1932,7 @@ hipError_t dispatch_bf16(int bm, const GemmArgs& a, hipStream_t s) {
         if (a.N % 128 == 0) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI, GROUPED>(a, s);
         return launch_bf16<256, 64, 4, 1, 64, 2, 1, EPI, GROUPED>(a, s);
     }
+    if (bm == 128) return launch_128<EPI, GROUPED>(a, s);
     if (bm == 64) return launch_64<EPI, GROUPED>(a, s);
     return hipErrorInvalidValue;
 }
@@ -1952,6 +1961,7 @@ hipError_t dispatch_tiled(int bm, const GemmArgs& a, hipStream_t s) {
         if (a.N % 128 == 0) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI, GROUPED>(a, s);
         return launch_bf16<256, 64, 4, 1, 64, 2, 1, EPI, GROUPED>(a, s);
     }
+    if (bm == 128) return launch_128<EPI, GROUPED>(a, s);
     if (bm == 64) {
         if (a.N % 128 == 0) return launch_bf16<64, 128, 1, 4, 64, 3, 2, EPI, GROUPED>(a, s);
         return launch_bf16<64, 64, 2, 2, 64, 3, 2, EPI, GROUPED>(a, s);
@@ -1968,6 +1978,10 @@ hipError_t dispatch_swiglu(int bm, GemmArgs a, hipStream_t s) {
         if (a.Kdim < 128 || (GROUPED && a.row_mode != ROWS_GATHER_TOKENS)) return hipErrorInvalidValue;
         a.N = 2 * ((a.act_ld + 127) / 128 * 128);
         return launch_pp<EPI_SWIGLU_STORE, GROUPED>(a, s);
+    }
+    if (bm == 128) {
+        a.N = 2 * a.act_ld;
+        return launch_bf16<128, 128, 2, 2, 64, 2, 2, EPI_SWIGLU_STORE, GROUPED>(a, s);
     }
     if (bm == 64) {
         a.N = 2 * a.act_ld;
@@ -1989,6 +2003,7 @@ hipError_t dispatch_swiglu_bwd(int bm, GemmArgs a, hipStream_t s) {
     }
     a.N = 2 * a.act_ld;
     if (bm == 256) return launch_bf16<256, 128, 2, 2, 64, 2, 1, EPI_SWIGLU_BWD, true>(a, s);
+    if (bm == 128) return launch_bf16<128, 128, 2, 2, 64, 2, 2, EPI_SWIGLU_BWD, true>(a, s);
     if (bm == 64) return launch_bf16<64, 128, 2, 2, 64, 3, 2, EPI_SWIGLU_BWD, true>(a, s);
     return hipErrorInvalidValue;
 }
@@ -2028,6 +2043,7 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
                 if (!GROUPED && gemm_combine_fusable(d, bm, a.N, a.Kdim) && a.route_k == d.K)
                 {
                     if (bm == 256) return launch_pp_combine(a, s);
+                    if (bm == 128) return launch_128<EPI_COMBINE, false>(a, s);
                     return launch_64<EPI_COMBINE, false>(a, s);
                 }
                 break;
@@ -2049,23 +2065,41 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
 
 }  // namespace
 
-int gemm_tile_bm(int32_t dtype, int64_t avg_rows) {
-    if (dtype != MOE_BF16) return 64;
-    return avg_rows >= 512 ? 256 : 64;
+int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows) {
+    if (d.dtype != MOE_BF16) return 64;
+    if (avg_rows >= 512) return 256;
+    // Where the padded rows weigh more: the 256-row tiles of the persistent
+    // kernel (widths it takes) from 320 rows, or from 128 where both layers'
+    // contractions are long (768 columns) beside its epilogue; else 128-row
+    // tiles from 192 rows where those fill the CUs' two places about twice (896
+    // tiles in the narrower layer). Layers, 256- and 128-row tiles: ViT-G widths, 160 rows
+    // 580 and 587 us, 320 rows 873 and 918; SwiGLU, 256 rows 1024 and 1091; ViT-H,
+    // 260 rows 160 and 167; ViT-L (h = 512), 131 rows 191 and 163, 250 rows 220 and
+    // 205, 448 rows 325 and 324. 64- and 128-row tiles: ViT-L, 131 rows 158 and 163,
+    // 200 rows (800 tiles) 188 and 190, 250 rows (1000) 212 and 201; ViT-B, 288 rows
+    // (432) 103 and 106; 64- and 256-row tiles: ViT-H, 130 rows 131 and 118,
+    // ViT-G, 160 rows 609 and 556, ViT-L, 448 rows 347 and 314.
+    const int hh = act_stride(d, d.h);
+    const bool pp = d.d % 128 == 0 && ((d.flags & MOE_FLAG_SWIGLU) || d.h % 128 == 0);
+    if (pp && (avg_rows >= 320 || (avg_rows >= 128 && d.d >= 768 && hh >= 768))) return 256;
+    const int64_t tiles = (int64_t)d.T * d.K / 128 * ((hh < d.d ? hh : d.d) / 128);
+    return avg_rows >= 192 && tiles >= 896 ? 128 : 64;
 }
 
 int gemm_dense_bm(int32_t dtype, int64_t rows, int32_t n) {
     if (dtype != MOE_BF16) return 64;
     // 256-row tiles only when they still give a few workgroups per CU.
     const int64_t tiles = (rows + 255) / 256 * (n / 256 > 0 ? n / 256 : 1);
-    return tiles >= 512 ? 256 : 64;
+    if (tiles >= 512) return 256;
+    // 128-row tiles where they still give most CUs two workgroups.
+    return (rows + 127) / 128 * (n / 128 > 0 ? n / 128 : 1) >= 384 ? 128 : 64;
 }
 
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim) {
     // The persistent 256 x 256 kernel with its combine epilogue, or the
     // 64-row tiled kernel with its own (K <= 8 either way).
     if (d.dtype != MOE_BF16 || d.K > kMaxCombineK) return false;
-    return (bm == 256 && n % 256 == 0 && kdim >= 128) || (bm == 64 && n % 64 == 0);
+    return (bm == 256 && n % 256 == 0 && kdim >= 128) || (bm <= 128 && n % 64 == 0);
 }
 
 hipError_t launch_gemm(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a, hipStream_t s) {

@@ -188,7 +188,7 @@ WorkspacePlan plan_workspace(const moe_desc_t& d) {
     const size_t es = elem_size(d.dtype);
     const size_t TK = (size_t)d.T * d.K;
     p.n_hist_blocks = permute_blocks((int64_t)TK, d.E);
-    p.tile_bm = gemm_tile_bm(d.dtype, (int64_t)TK / d.E);
+    p.tile_bm = gemm_tile_bm(d, (int64_t)TK / d.E);
     // The SwiGLU first layer runs on 256-row tiles only with two or more K slabs.
     if ((d.flags & MOE_FLAG_SWIGLU) && d.d < 128) p.tile_bm = 64;
     const size_t busy = TK < (size_t)d.E ? TK : (size_t)d.E;  // experts that can hold a slot

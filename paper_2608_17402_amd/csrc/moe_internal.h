@@ -139,7 +139,7 @@ struct BackwardPlan {
 };
 BackwardPlan plan_backward(const moe_desc_t& d);
 // M-tile height of the grouped GEMM for groups of `avg_rows` rows on average.
-int gemm_tile_bm(int32_t dtype, int64_t avg_rows);
+int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows);
 // Row stride of an expert activation of hidden width h: h itself for GELU
 // experts, h rounded up to a multiple of 64 for SwiGLU experts (the padding
 // columns hold zeros, and the second layer's weights have the same stride).
