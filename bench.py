@@ -482,7 +482,7 @@ def main():
         return {
             "workload": c.name, "act": c.act, "entry": "moe_grouped_mlp_backward", "us": round(b_ms * 1e3, 1),
             "tokens_per_s": round(c.T / (b_ms * 1e-3), 1),
-            "roofline": {"kernel": "expert-MLP backward: fc1 again, dA, dx, dW2, dW1 products plus transposes",
+            "roofline": {"kernel": "expert-MLP backward: fc1 again, dA, dx, dW2, dW1 products plus the slot sum",
                          "bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(tf / PEAK_BF16_TFLOPS, 4), "traffic": backward_traffic_bytes(c.name),
                          "algorithmic_flops_per_launch": fl, "avg_launch_us": round(b_ms * 1e3, 2)},
