@@ -15,11 +15,13 @@
 // meet in the same L2.
 //
 // bf16: v_mfma_f32_32x32x16_bf16 with fp32 accumulators. Both operands are
-// K-contiguous (token rows and nn.Linear weight rows) and stream global -> LDS
+// K-contiguous (token rows and nn.Linear weight rows; the backward's dA and dx
+// contract along the weight rows and read their fragments with the transposing
+// LDS reads, as wgrad.hip does) and stream global -> LDS
 // in 64-wide K slabs through rings of a few slabs (buffer_load ... lds), with
 // 16-byte chunks XOR-swizzled by row so that the rows a fragment read touches
 // spread over the LDS banks. The kernels:
-//   k_gemm_bf16  tiled, one tile per workgroup (256- or 64-row tiles, 64- to
+//   k_gemm_bf16  tiled, one tile per workgroup (256-, 128- or 64-row tiles, 64- to
 //                256-column tiles); every epilogue, including the backward's
 //   k_gemm_sp    256 x 256 tiles, four waves of 128 x 128, copies paced by
 //                hand against the MFMAs (used where K is one slab)
@@ -30,7 +32,7 @@
 // Epilogues (EPI_*): GELU or SwiGLU to bf16 (first layer), scatter to slot
 // order (second layer), fp32 store, the gate-weighted combine, and the
 // backward's recompute (with fp32 pre-activations), dA through GELU' or
-// SwiGLU', fp32 slot gradients and fp32 weight gradients.
+// SwiGLU' and fp32 slot gradients.
 #include "gemm_device.h"
 #include "moe_internal.h"
 
@@ -1904,7 +1906,7 @@ hipError_t launch_128(const GemmArgs& a, hipStream_t s) {
 
 // Tile shapes. Large groups (M-tiles of 256 token rows): 256 x 256 on the
 // persistent kernel when N allows and K spans at least two slabs (the paced
-// one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Small
+// one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Between (gemm_tile_bm) 128-row tiles. Small
 // groups (M-tiles of 64 rows, the weight-read-bound regime where an expert
 // sees a few dozen tokens): 64 x 128 or 64 x 64 with three slabs in the ring
 // and several workgroups per CU, to keep many weight loads in flight.

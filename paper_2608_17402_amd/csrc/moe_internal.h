@@ -50,11 +50,11 @@ enum GemmEpilogue : int {
                             // act_ld (C's row stride): B holds per group the act_n gate rows, then
                             // the act_n up rows. The launcher sets N: a tile of BN columns computes
                             // BN / 2 activation columns from the matching gate and up rows
-    // Backward of GELU experts (tiled kernel only):
+    // Backward of GELU experts:
     EPI_GELU_BWD = 5,       // C[p, :] = bf16(GELU(acc)) and C2[p, :] = acc (fp32), sorted order
     EPI_DGELU = 6,          // C[p, :] = bf16(acc * GELU'(aux[p, :])) (aux fp32 [rows, N]), sorted order
     EPI_SCATTER_SLOT_F32 = 7,  // C[sorted_slots[p], :] = acc as fp32
-    // Backward of SwiGLU experts (tiled kernel only):
+    // Backward of SwiGLU experts:
     EPI_SWIGLU_BWD = 9,     // EPI_SWIGLU_STORE, and the fp32 gate and up pre-activations into C2
                             // [rows, 2 act_ld]: G at column c, U at column act_ld + c
     EPI_DSWIGLU = 10,       // dA = acc (N = act_ld columns); with G, U from aux [rows, 2 act_ld] (fp32):
