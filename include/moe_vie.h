@@ -107,7 +107,9 @@ moe_status_t moe_workspace_size(const moe_desc_t *desc, size_t *bytes);
  *   bias      [E] fp32 or NULL (= 0): added to the sigmoid score for
  *             selection only
  *   topk_idx  [T, K] int32 out: chosen experts, in descending selection key
- *             (Sigmoid(s_e) + b_e); equal keys go to the lower expert index
+ *             (Sigmoid(s_e) + b_e); equal keys go to the lower expert index.
+ *             The K experts are distinct and in [0, E) whatever the inputs
+ *             hold: a NaN key (from inputs that are not finite) counts as -inf
  *   topk_gate [T, K] fp32 out: Sigmoid(s_e) / sum of Sigmoid over the chosen
  * Arithmetic is fp32 and reproducible bit for bit: each logit is one fused
  * multiply-add chain over i = 0..d-1 in ascending order starting from +0;

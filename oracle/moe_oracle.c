@@ -148,7 +148,8 @@ void oracle_scores(int T, int d, int E, const float *x, const float *wr, float *
 
 /* Top-K of one token from its sigmoid scores sig[E] and the selection bias
  * (Eq. (7)); gates renormalise the unbiased scores of the chosen experts
- * (Eq. (5)). Key a beats key b when a > b, or a == b and a's index is lower. */
+ * (Eq. (5)). Key a beats key b when a > b, or a == b and a's index is lower;
+ * a NaN key counts as -inf. */
 static void select_topk(int E, int K, const float *sig, const float *bias,
                         int32_t *idx, float *gate, unsigned char *taken) {
     memset(taken, 0, (size_t)E);
@@ -158,6 +159,7 @@ static void select_topk(int E, int K, const float *sig, const float *bias,
         for (int e = 0; e < E; ++e) {
             if (taken[e]) continue;
             float key = bias ? sig[e] + bias[e] : sig[e];
+            if (isnan(key)) key = -INFINITY;
             if (best < 0 || key > best_key) { best = e; best_key = key; }
         }
         taken[best] = 1;

@@ -69,6 +69,17 @@ __device__ __forceinline__ void load8(const float* p, float* v) {
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
+// Rank of a selection key as an unsigned integer of the same order, from
+// 0x007fffff for -inf up; a NaN counts as -inf (fmaxf returns the number).
+// Every selection below compares ranks, with 0 for an unused or taken place,
+// so a damaged key never displaces a sound one and K distinct experts in range
+// come out whatever the keys are. (A key of -0 cannot occur: the sigmoid is
+// positive, and a sum that cancels rounds to +0.)
+__device__ __forceinline__ uint32_t key_rank(float key) {
+    const uint32_t u = __float_as_uint(fmaxf(key, -INFINITY));
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
 // Top-K selection and gates, one wavefront per token. Lane l holds experts
 // l, l + 64, ...; each of the K rounds takes the wave-wide best (key
 // descending, expert index ascending on equal keys) with a butterfly of
@@ -83,13 +94,14 @@ __global__ __launch_bounds__(256) void k_topk(const float* __restrict__ logits, 
     const int t = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (t >= T) return;  // uniform per wave
     const int per = (E + kWave - 1) / kWave;
-    float sig[kPerLane], key[kPerLane];
+    float sig[kPerLane];
+    uint32_t key[kPerLane];
 #pragma unroll
     for (int m = 0; m < kPerLane; ++m) {
         const int e = lane + kWave * m;
         const bool ok = m < per && e < E;
         sig[m] = ok ? sigmoid_fp32(logits[(size_t)t * ld + e]) : 0.0f;
-        key[m] = ok ? (bias ? sig[m] + bias[e] : sig[m]) : -INFINITY;
+        key[m] = ok ? key_rank(bias ? sig[m] + bias[e] : sig[m]) : 0u;
     }
     uint32_t taken = 0;
     float csig[kMaxK];
@@ -99,7 +111,7 @@ __global__ __launch_bounds__(256) void k_topk(const float* __restrict__ logits, 
         csig[j] = 0.0f;
         cidx[j] = 0;
         if (j >= K) continue;
-        float bk = -INFINITY;
+        uint32_t bk = 0u;
         int be = 0x7fffffff;
         float bs = 0.0f;
 #pragma unroll
@@ -115,7 +127,7 @@ __global__ __launch_bounds__(256) void k_topk(const float* __restrict__ logits, 
         }
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) {
-            const float ok = __shfl_xor(bk, off);
+            const uint32_t ok = __shfl_xor(bk, off);
             const int oe = __shfl_xor(be, off);
             const float os = __shfl_xor(bs, off);
             if (ok > bk || (ok == bk && oe < be)) {
@@ -471,11 +483,10 @@ __device__ __forceinline__ uint32_t row16_umax(uint32_t v) {
 }
 
 // Sigmoids, top-K and gates from exact logits for up to 16 PER experts: 16
-// lanes per token (lane g holds experts g PER ..), 4 tokens per wave. Keys
-// compare as integers of the same order (an unused or taken slot is 0, below
-// every key); each of the K rounds takes the group's largest key, lowest lane
-// and then lowest expert on ties. The winners' experts and the token's
-// sigmoids meet in LDS for the denominator in slot order.
+// lanes per token (lane g holds experts g PER ..), 4 tokens per wave. Each of
+// the K rounds takes the group's largest key rank, lowest lane and then lowest
+// expert on ties. The winners' experts and the token's sigmoids meet in LDS
+// for the denominator in slot order.
 template <int PER>
 __global__ __launch_bounds__(256) void k_topk16(const float* __restrict__ logits, int ld,
                                                const float* __restrict__ bias, int T, int E, int K,
@@ -496,8 +507,7 @@ __global__ __launch_bounds__(256) void k_topk16(const float* __restrict__ logits
 #pragma unroll
     for (int m = 0; m < PER; ++m) {
         s[m] = sigmoid_fp32(s[m]);
-        const uint32_t u = __float_as_uint(bias ? s[m] + b[m] : s[m]);
-        key[m] = e0 + m < E ? ((u & 0x80000000u) ? ~u : (u | 0x80000000u)) : 0u;
+        key[m] = e0 + m < E ? key_rank(bias ? s[m] + b[m] : s[m]) : 0u;
     }
 #pragma unroll
     for (int m = 0; m < PER; m += 4)
@@ -536,7 +546,10 @@ __global__ __launch_bounds__(256) void k_topk16(const float* __restrict__ logits
 // lower end of the key intervals; the candidates are the experts whose upper
 // end reaches L, written to cand[t][0 .. NS) (in no particular order) with
 // their count in ncand[t]. A token with more than NS candidates gets
-// ncand = -1 and is appended to the overflow queue.
+// ncand = -1 and is appended to the overflow queue. An interval without
+// numbers (a NaN logit, norm or bias) reaches from -inf to +inf: it raises no
+// L, and its expert is a candidate, whose exact key decides; the interval of
+// a -inf bias is that one point.
 template <int LPA, int PER, int NS, bool SPLIT>
 __global__ __launch_bounds__(256) void k_router_cand(const float* __restrict__ s_fast,
                                                     const bf16_t* __restrict__ x,
@@ -634,8 +647,8 @@ __global__ __launch_bounds__(256) void k_router_cand(const float* __restrict__ s
         const bool ok = live && e0 + m < E;
         const float key = sigmoid_fast(sf[m]) + bv[m];
         const float delta = 0.25f * (cst * xn * wn[m]) + 4e-6f + 1e-6f * fabsf(bv[m]);
-        lo[m] = ok ? key - delta : -INFINITY;
-        hi[m] = ok ? key + delta : -INFINITY;
+        lo[m] = ok ? fmaxf(key - delta, -INFINITY) : -INFINITY;  // fmaxf: the number, if one is a NaN
+        hi[m] = ok ? fmaxf(key + delta, key) : -INFINITY;
     }
     // L: the K-th largest of the lanes' three largest lower ends. These are a
     // subset of all lower ends, so L is at most the K-th largest lower end and
@@ -664,7 +677,7 @@ __global__ __launch_bounds__(256) void k_router_cand(const float* __restrict__ s
         // (an inclusive scan of the lanes' counts along the 16-lane DPP row).
         uint32_t cbits = 0;
 #pragma unroll
-        for (int m = 0; m < PER; ++m) cbits |= (live && hi[m] >= L) ? (1u << m) : 0u;
+        for (int m = 0; m < PER; ++m) cbits |= (live && !(hi[m] < L)) ? (1u << m) : 0u;
         const int cnt = __popc(cbits);
         int incl = cnt;
         incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, false);  // row_shr:1
@@ -681,7 +694,7 @@ __global__ __launch_bounds__(256) void k_router_cand(const float* __restrict__ s
         const uint64_t below = grp & ((1ull << lane) - 1ull);
 #pragma unroll
         for (int m = 0; m < PER; ++m) {
-            const bool c = live && hi[m] >= L;
+            const bool c = live && !(hi[m] < L);
             const uint64_t bal = __ballot(c) & grp;
             if (c) {
                 const int pos = nc + __popcll(bal & below);
@@ -703,8 +716,8 @@ __global__ __launch_bounds__(256) void k_router_cand(const float* __restrict__ s
 // Exact top-K of a token's candidates and their gates, for the chain kernels
 // (TPB tokens of LPT lanes, CPL chains per lane; candidate slot g + LPT c of
 // token tl holds expert ec[c] with exact logit acc[c]). Every candidate's key
-// (sigmoid plus selection bias), sigmoid and expert go to LDS; each lane
-// ranks its own candidates among the token's in (key descending, expert
+// (the rank of sigmoid plus selection bias), sigmoid and expert go to LDS; each
+// lane ranks its own candidates among the token's in (key descending, expert
 // ascending) order, the order of taking the K largest keys one by one; ranks
 // below K are the slots. Then every lane of the token forms the gate
 // denominator in slot order and writes its slots. Called by every thread of
@@ -716,20 +729,21 @@ __device__ __forceinline__ void chain_select(uint8_t* lds, int tl, int g, int t,
                                              const float (&bc)[CPL], bool has_bias, int32_t* __restrict__ topk_idx,
                                              float* __restrict__ topk_gate) {
     constexpr int NS = LPT * CPL;
-    float* skey = reinterpret_cast<float*>(lds);
-    float* ssig = skey + TPB * NS;
+    uint32_t* skey = reinterpret_cast<uint32_t*>(lds);
+    float* ssig = reinterpret_cast<float*>(skey + TPB * NS);
     int* sexp = reinterpret_cast<int*>(ssig + TPB * NS);
     float* osig = reinterpret_cast<float*>(sexp + TPB * NS);
     int* oexp = reinterpret_cast<int*>(osig + TPB * kMaxK);
-    float kc[CPL], sc[CPL];
+    uint32_t kc[CPL];
+    float sc[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
         const int j = g + LPT * c;
         sc[c] = 0.0f;
-        kc[c] = 0.0f;
+        kc[c] = 0u;
         if (on[c]) {
             sc[c] = sigmoid_fp32(acc[c]);
-            kc[c] = has_bias ? sc[c] + bc[c] : sc[c];
+            kc[c] = key_rank(has_bias ? sc[c] + bc[c] : sc[c]);
             skey[tl * NS + j] = kc[c];
             ssig[tl * NS + j] = sc[c];
             sexp[tl * NS + j] = ec[c];
@@ -739,11 +753,11 @@ __device__ __forceinline__ void chain_select(uint8_t* lds, int tl, int g, int t,
     // The token's NS keys and experts in 16-byte reads (slots from nc on are
     // read but not counted).
     static_assert(NS % 4 == 0, "whole 16-byte reads");
-    float kq[NS];
+    uint32_t kq[NS];
     int eq[NS];
 #pragma unroll
     for (int q = 0; q < NS; q += 4) {
-        const float4 k4 = *reinterpret_cast<const float4*>(skey + tl * NS + q);
+        const uint4 k4 = *reinterpret_cast<const uint4*>(skey + tl * NS + q);
         const int4 e4 = *reinterpret_cast<const int4*>(sexp + tl * NS + q);
         kq[q] = k4.x, kq[q + 1] = k4.y, kq[q + 2] = k4.z, kq[q + 3] = k4.w;
         eq[q] = e4.x, eq[q + 1] = e4.y, eq[q + 2] = e4.z, eq[q + 3] = e4.w;
@@ -785,13 +799,14 @@ __device__ __forceinline__ void exact_select_wave(const float* sig, const float*
                                                   int t, int lane, int32_t* __restrict__ topk_idx,
                                                   float* __restrict__ topk_gate) {
     const int per = (E + kWave - 1) / kWave;
-    float sg[kPerLane], key[kPerLane];
+    float sg[kPerLane];
+    uint32_t key[kPerLane];
 #pragma unroll
     for (int m = 0; m < kPerLane; ++m) {
         const int e = lane + kWave * m;
         const bool ok = m < per && e < E;
         sg[m] = ok ? sig[e] : 0.0f;
-        key[m] = ok ? (bias ? sg[m] + bias[e] : sg[m]) : -INFINITY;
+        key[m] = ok ? key_rank(bias ? sg[m] + bias[e] : sg[m]) : 0u;
     }
     uint32_t taken = 0;
     float csig[kMaxK];
@@ -801,7 +816,7 @@ __device__ __forceinline__ void exact_select_wave(const float* sig, const float*
         csig[j] = 0.0f;
         cidx[j] = 0;
         if (j >= K) continue;
-        float bk = -INFINITY;
+        uint32_t bk = 0u;
         int be = 0x7fffffff;
         float bs = 0.0f;
 #pragma unroll
@@ -815,7 +830,7 @@ __device__ __forceinline__ void exact_select_wave(const float* sig, const float*
         }
 #pragma unroll
         for (int off = kWave / 2; off > 0; off >>= 1) {
-            const float ok = __shfl_xor(bk, off);
+            const uint32_t ok = __shfl_xor(bk, off);
             const int oe = __shfl_xor(be, off);
             const float os = __shfl_xor(bs, off);
             if (ok > bk || (ok == bk && oe < be)) {
