@@ -38,6 +38,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -2067,25 +2069,53 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
 
 }  // namespace
 
-int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows) {
+// Share of a 256-CU part's time that the persistent kernel's 256 x 256 tiles
+// would spend on real rows and columns of the two grouped layers, for loads
+// known by their mean alone. A pass over the CUs costs its slabs and about nine
+// more (pipeline fill and epilogue), whether every CU has a tile or not. The
+// tiles: half a ragged tile per expert and a standard deviation of it, or, for
+// loads close to the mean, those of experts with Poisson counts.
+static double fill256(const moe_desc_t& d) {
+    constexpr int kCus = 256, kTail = 9;
+    const bool swiglu = d.flags & MOE_FLAG_SWIGLU;
+    const int hh = act_stride(d, d.h);
+    const double slots = (double)d.T * d.K, rows = slots / d.E, full = slots / 256;
+    auto above = [&](int n) { return 0.5 * std::erfc((n - rows) / std::sqrt(2 * rows)); };  // P(count > n)
+    const double tiles = std::max(full + 0.5 * (d.E + std::sqrt((double)d.E)), d.E * (1 + above(256) + above(512)));
+    double work = 0, time = 0;
+    auto layer = [&](int n, int cols, int k) {
+        work += full * n / 256 * (k / 64);
+        time += std::ceil(tiles * cols / kCus) * kCus * (k / 64 + kTail);
+    };
+    layer(swiglu ? 2 * hh : hh, swiglu ? (hh + 127) / 128 : (hh + 255) / 256, d.d);
+    layer(d.d, (d.d + 255) / 256, hh);
+    return work / time;
+}
+
+int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows, bool backward) {
     if (d.dtype != MOE_BF16) return 64;
     if (avg_rows >= 512) return 256;
-    // Where the padded rows weigh more: the 256-row tiles of the persistent
-    // kernel (widths it takes) from 320 rows, or from 128 where both layers'
-    // contractions are long (768 columns) beside its epilogue; else 128-row
-    // tiles from 192 rows where those fill the CUs' two places about twice (896
-    // tiles in the narrower layer). Layers, 256- and 128-row tiles: ViT-G widths, 160 rows
-    // 580 and 587 us, 320 rows 873 and 918; SwiGLU, 256 rows 1024 and 1091; ViT-H,
-    // 260 rows 160 and 167; ViT-L (h = 512), 131 rows 191 and 163, 250 rows 220 and
-    // 205, 448 rows 325 and 324. 64- and 128-row tiles: ViT-L, 131 rows 158 and 163,
-    // 200 rows (800 tiles) 188 and 190, 250 rows (1000) 212 and 201; ViT-B, 288 rows
-    // (432) 103 and 106; 64- and 256-row tiles: ViT-H, 130 rows 131 and 118,
-    // ViT-G, 160 rows 609 and 556, ViT-L, 448 rows 347 and 314.
-    const int hh = act_stride(d, d.h);
+    // With fewer rows the 256-row tiles (widths the persistent kernel takes, from
+    // 128 rows) only where they fill enough of the chip, whatever the loads: a
+    // few experts or narrow layers leave most CUs without a tile, and ragged or
+    // skewed loads pad (8 experts, d = h = 768, 130 rows: 64-row tiles 17 us for
+    // the two products, 256-row tiles 46; 128 experts, d = h = 512, 130 rows,
+    // skewed: 54 and 76). Over 1100 shapes of 4 to 200 experts, 128 to 511 rows,
+    // widths 256 to 1536, balanced and skewed, no forward pair lost against
+    // 64-row tiles where the fill is 0.30 or more (1.00 to 1.50 times as fast; at
+    // 0.28, 0.76 at the least), no backward from 0.34 (its products have the
+    // longer epilogues). ViT-H, 260 rows (0.32): 166 and 155 us a layer; ViT-L,
+    // 448 rows (0.35): 335 and 311; ViT-G, 160 rows (0.32): 609 and 556.
+    const int hh = act_stride(d, d.h), width = hh < d.d ? hh : d.d;
     const bool pp = d.d % 128 == 0 && ((d.flags & MOE_FLAG_SWIGLU) || d.h % 128 == 0);
-    if (pp && (avg_rows >= 320 || (avg_rows >= 128 && d.d >= 768 && hh >= 768))) return 256;
-    const int64_t tiles = (int64_t)d.T * d.K / 128 * ((hh < d.d ? hh : d.d) / 128);
-    return avg_rows >= 192 && tiles >= 896 ? 128 : 64;
+    if (pp && avg_rows >= 128 && fill256(d) >= (backward ? 0.35 : 0.31)) return 256;
+    // 128-row tiles from 192 rows where those fill the CUs' two places about
+    // twice (896 tiles in the narrower layer) and no layer is only 256 columns
+    // wide (200 experts, d = h = 256, 330 rows: 64-row tiles 55 us, 128-row tiles
+    // 57). ViT-L, 64- and 128-row tiles: 131 rows 158 and 163, 200 rows (800
+    // tiles) 188 and 190, 250 rows (1000) 212 and 201.
+    const int64_t tiles = (int64_t)d.T * d.K / 128 * (width / 128);
+    return avg_rows >= 192 && width >= 320 && tiles >= 896 ? 128 : 64;
 }
 
 int gemm_dense_bm(int32_t dtype, int64_t rows, int32_t n) {

@@ -183,12 +183,12 @@ static bool router_norms_in_gemm(const moe_desc_t& d) {
            d.d >= 128 && router_splits(d) == 1;
 }
 
-WorkspacePlan plan_workspace(const moe_desc_t& d) {
+WorkspacePlan plan_workspace(const moe_desc_t& d, bool backward) {
     WorkspacePlan p;
     const size_t es = elem_size(d.dtype);
     const size_t TK = (size_t)d.T * d.K;
     p.n_hist_blocks = permute_blocks((int64_t)TK, d.E);
-    p.tile_bm = gemm_tile_bm(d, (int64_t)TK / d.E);
+    p.tile_bm = gemm_tile_bm(d, (int64_t)TK / d.E, backward);
     // The SwiGLU first layer runs on 256-row tiles only with two or more K slabs.
     if ((d.flags & MOE_FLAG_SWIGLU) && d.d < 128) p.tile_bm = 64;
     const size_t busy = TK < (size_t)d.E ? TK : (size_t)d.E;  // experts that can hold a slot
@@ -225,7 +225,7 @@ WorkspacePlan plan_workspace(const moe_desc_t& d) {
 
 BackwardPlan plan_backward(const moe_desc_t& d) {
     BackwardPlan b;
-    b.fwd = plan_workspace(d);
+    b.fwd = plan_workspace(d, true);
     const size_t TK = (size_t)d.T * d.K;
     b.ld = (int32_t)((TK + 128 * (size_t)d.E + 63) / 64 * 64);  // windows: >= 2 slabs, rounded up to one
     size_t off = b.fwd.total;

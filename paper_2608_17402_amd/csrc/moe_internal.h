@@ -116,7 +116,7 @@ size_t elem_size(int32_t dtype);
 // Records the message of a failing call (read back by moe_last_error) and
 // returns `st`.
 moe_status_t set_last_error(moe_status_t st, const char* fmt, ...);
-WorkspacePlan plan_workspace(const moe_desc_t& d);
+WorkspacePlan plan_workspace(const moe_desc_t& d, bool backward = false);
 
 // Workspace of the expert-MLP backward: the forward plan (tile table,
 // activation), then the backward's own regions.
@@ -138,8 +138,8 @@ struct BackwardPlan {
     size_t total;
 };
 BackwardPlan plan_backward(const moe_desc_t& d);
-// M-tile height of the grouped GEMM for groups of `avg_rows` rows on average.
-int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows);
+// M-tile height of the grouped GEMMs for groups of `avg_rows` rows on average.
+int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows, bool backward);
 // Row stride of an expert activation of hidden width h: h itself for GELU
 // experts, h rounded up to a multiple of 64 for SwiGLU experts (the padding
 // columns hold zeros, and the second layer's weights have the same stride).

@@ -1,0 +1,130 @@
+"""The grouped products on each tile height that the rules pick below 512 rows
+an expert, forward and backward: 256-row tiles (a few experts to many, 180 to
+500 rows, widths that are rounded up to the 256-column tile), 128-row tiles
+(128 x 128 and 128 x 64, GELU and SwiGLU, widths that are odd multiples of 64 or
+no multiple of 64), 64-row tiles one row short of either, each with balanced and
+skewed loads (experts without rows among them).
+
+Every row against torch in 64 bits, with the activation (and in the backward
+the pre-activation gradient) rounded to bf16 where the library rounds it. What
+remains is the result's own rounding (2^-9 of a value), one-ulp flips of the
+rounded intermediates and fp32 sums, so the bounds are those of the oracle
+tests: 2e-2 of the largest value and 5e-3 in the 2-norm."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_17402_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+# T, d, E, K, h, act
+FORWARD = {
+    "h256_500rows": (6000, 512, 48, 4, 512, "gelu"),
+    "h256_rounded_640": (4000, 640, 32, 4, 640, "gelu"),
+    "h256_180rows": (2160, 1024, 48, 4, 1024, "gelu"),
+    "h256_sw_180rows": (1440, 1280, 32, 4, 710, "swiglu"),
+    "h256_sw_250rows": (2000, 1280, 32, 4, 500, "swiglu"),
+    "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
+    "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
+    "h128_sw_d576": (7200, 576, 128, 4, 500, "swiglu"),
+    "h64_895tiles": (7167, 512, 128, 4, 512, "gelu"),
+    "h64_4experts": (900, 768, 4, 2, 768, "gelu"),
+    "h64_narrow": (15000, 256, 128, 4, 256, "gelu"),
+}
+BACKWARD = {
+    "h256_rounded_640": (4000, 768, 32, 4, 640, "gelu"),
+    "h256_250rows": (2000, 1280, 32, 4, 1024, "gelu"),
+    "h256_sw": (1440, 1536, 32, 4, 710, "swiglu"),
+    "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
+    "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
+    "h128_sw": (7200, 512, 128, 4, 500, "swiglu"),
+    "h128_sw_d576": (7200, 576, 128, 4, 500, "swiglu"),
+    "h64_8experts": (1400, 512, 8, 2, 512, "gelu"),
+    "h64_sw_16experts": (1300, 1280, 16, 4, 854, "swiglu"),
+}
+
+
+def _setup(case, skew, seed):
+    T, d, E, K, h, act = case
+    sw = act == "swiglu"
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+
+    def normal(*shape, std):
+        return (torch.randn(*shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+
+    key = torch.rand(T, E, generator=gen, device="cuda")
+    if skew:  # the last experts get most tokens, the first eighth none
+        key = key + torch.linspace(0, 0.8, E, device="cuda")
+        key[:, : E // 8] = -1.0
+    idx = key.topk(K, dim=1).indices.to(torch.int32).contiguous()
+    ldh = -(-h // 64) * 64 if sw else h
+    w1, w2 = normal(E, (2 if sw else 1) * h, d, std=0.05), torch.zeros(E, d, ldh, dtype=torch.bfloat16, device="cuda")
+    w2[..., :h] = normal(E, d, h, std=0.05)
+    x, g = normal(T, d, std=1.0), normal(T * K, d, std=0.5)
+    desc = binding.make_desc(T, d, E, K, h, 0, 1.0, "bf16", flags=binding.MOE_FLAG_SWIGLU if sw else 0)
+    ws = binding.alloc_workspace(desc)
+    counts, offsets, slots = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * K))
+    binding.moe_permute(desc, idx, counts, offsets, slots, ws)
+    return desc, ws, x, w1, w2, g, offsets, slots
+
+
+def _act(p, h, sw):
+    """Activation and its derivatives from fp64 pre-activations."""
+    if sw:
+        a, u = p[:, :h], p[:, h:]
+        s = torch.sigmoid(a)
+        return a * s * u, (u * s * (1 + a * (1 - s)), a * s)
+    phi = 0.5 * (1 + torch.erf(p * 0.5 ** 0.5))
+    return p * phi, (phi + p * torch.exp(-0.5 * p * p) * 0.3989422804014327,)
+
+
+def _close(got, ref, what):
+    got = got.double()
+    assert bool(torch.isfinite(got).all()), what
+    err, scale = got - ref, max(1.0, float(ref.abs().max()))
+    max_abs, rel = float(err.abs().max()), float(err.norm() / ref.norm())
+    assert max_abs <= 2e-2 * scale and rel <= 5e-3, f"{what}: max_abs={max_abs:.3e} (scale {scale:.2f}), rel={rel:.3e}"
+
+
+@pytest.mark.parametrize("skew", [False, True], ids=["balanced", "skewed"])
+@pytest.mark.parametrize("name", FORWARD)
+def test_grouped_forward(name, skew):
+    T, d, E, K, h, act = FORWARD[name]
+    desc, ws, x, w1, w2, _, offsets, slots = _setup(FORWARD[name], skew, 11)
+    out = torch.full((T * K, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    binding.moe_grouped_mlp(desc, x, slots, offsets, w1, w2, out, ws)
+    ref = torch.empty(T * K, d, dtype=torch.float64, device="cuda")
+    ends = offsets.tolist()
+    for e in range(E):
+        sl = slots[ends[e]:ends[e + 1]].long()
+        a, _ = _act(x[sl // K].double() @ w1[e].double().t(), h, act == "swiglu")
+        ref[sl] = a.to(torch.bfloat16).double() @ w2[e, :, :h].double().t()
+    _close(out, ref, name)
+
+
+@pytest.mark.parametrize("skew", [False, True], ids=["balanced", "skewed"])
+@pytest.mark.parametrize("name", BACKWARD)
+def test_grouped_backward(name, skew):
+    T, d, E, K, h, act = BACKWARD[name]
+    desc, _, x, w1, w2, g, offsets, slots = _setup(BACKWARD[name], skew, 12)
+    bws = binding.alloc_backward_workspace(desc)
+    dx = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dw1, dw2 = (torch.full(w.shape, float("nan"), device="cuda") for w in (w1, w2))
+    binding.moe_grouped_mlp_backward(desc, x, slots, offsets, w1, w2, g, dx, dw1, dw2, bws)
+    rdx = torch.zeros(T, d, dtype=torch.float64, device="cuda")
+    r1, r2 = (torch.zeros(w.shape, dtype=torch.float64, device="cuda") for w in (w1, w2))
+    ends = offsets.tolist()
+    for e in range(E):
+        sl = slots[ends[e]:ends[e + 1]].long()
+        xe, ge = x[sl // K].double(), g[sl].double()
+        a, grads = _act(xe @ w1[e].double().t(), h, act == "swiglu")
+        da = ge @ w2[e, :, :h].double()
+        dh = torch.cat([da * q for q in grads], dim=1).to(torch.bfloat16).double()
+        rdx.index_add_(0, sl // K, dh @ w1[e].double())
+        r1[e], r2[e, :, :h] = dh.t() @ xe, ge.t() @ a.to(torch.bfloat16).double()
+    _close(dx, rdx, f"{name} dx")
+    _close(dw1, r1, f"{name} dw1")
+    _close(dw2, r2, f"{name} dw2")
+    assert not bool(dw2[..., h:].any())

@@ -1,9 +1,9 @@
-"""Layers at the edges of the rules that pick the GEMM tiles and rings: rows per
-expert around 128, 192 and 320, contractions around 768 columns, widths the
-persistent kernel does not take, dense shared layers on 128-row tiles, and
-launches of a few tiles (deep rings, fewer K slabs than the ring holds). Every
-token against the oracle, forward and backward, with the bounds of the random
-shapes (routing bit for bit)."""
+"""Layers of a few experts with ragged row counts (64-row tiles: the 256-row
+tiles would leave most CUs idle), layers on either side of the 128-row tiles'
+line (896 tiles), dense shared layers with K = 1, and launches of a few tiles
+(deep rings, fewer K slabs than the ring holds). Every token against the
+oracle, forward and backward, with the bounds of the random shapes (routing bit
+for bit). The tile heights of larger groups: test_gpu_tile_heights."""
 
 import pytest
 
