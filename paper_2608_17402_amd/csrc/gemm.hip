@@ -44,9 +44,9 @@
 #include <utility>
 
 namespace moe {
-// Workgroups of the persistent kernel: one per CU (a multiple of the XCD
+// Workgroups of a persistent kernel: per_cu per CU (a multiple of the XCD
 // count), fewer when the grid-sizing bound on the tiles is smaller.
-int persistent_grid(long long tile_bound) {
+int persistent_grid(long long tile_bound, int per_cu) {
     static int cus[64] = {0};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
@@ -57,7 +57,8 @@ int persistent_grid(long long tile_bound) {
         cus[dev] = n / kNumXcd * kNumXcd;
     }
     const long long bound = (tile_bound + kNumXcd - 1) / kNumXcd * kNumXcd;
-    return (int)(bound < cus[dev] ? bound : cus[dev]);
+    const long long most = (long long)per_cu * cus[dev];
+    return (int)(bound < most ? bound : most);
 }
 
 namespace {

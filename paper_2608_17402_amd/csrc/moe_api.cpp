@@ -489,6 +489,7 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
         w.N = n;
         w.h = half;
         w.items_max = b.items_max;
+        w.items_mean = d.E * (int32_t)((TK / d.E + 64 * kWgradSlabs) / (64 * kWgradSlabs));
         w.gather_bytes = (uint32_t)((gather_a ? TK : (size_t)d.T) * d.d * 2);
         HIP_CHECK(launch_wgrad(w, gather_a, s), what);
         HIP_CHECK(launch_wgrad_reduce(partials, rlist, wcount, d.E, (size_t)(half ? 2 * half : m) * n, out, s), what);

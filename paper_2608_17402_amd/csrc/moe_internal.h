@@ -211,13 +211,14 @@ struct WgradArgs {
     int32_t M, N;             // multiples of 64
     int32_t h;                // > 0: A holds gate and up columns, M / 2 each, of which h exist
     int32_t items_max;        // bound on the work items (grid sizing)
+    int32_t items_mean;       // work items of balanced loads (tile choice)
     uint32_t gather_bytes;    // bytes of the gathered operand
 };
 // dW = A^T B per expert (wgrad.hip): A gathered and B in sorted order
 // (gather_a), or the other way round.
 hipError_t launch_wgrad(const WgradArgs& a, bool gather_a, hipStream_t s);
-// Workgroups of a persistent kernel with at most tile_bound tiles.
-int persistent_grid(long long tile_bound);
+// Workgroups of a persistent kernel with at most tile_bound tiles, per_cu of them on a CU.
+int persistent_grid(long long tile_bound, int per_cu = 1);
 hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
                              int32_t* wcount, hipStream_t s);
 hipError_t launch_wgrad_reduce(const float* partials, const TileDesc* rlist, const int32_t* wcount, int E,

@@ -15,15 +15,18 @@ namespace {
 
 // Persistent 256 x 256 tiles, as k_gemm_pp: four waves of 128 x 128, a ring of
 // three slabs for A and of two for B (160 KB), copies paced against the MFMAs,
-// the slab pipeline running on across tiles.
+// the slab pipeline running on across tiles. TS = 128: tiles of 128 x 128, waves
+// of 64 x 64, 80 KB and so two workgroups per CU, for launches that have few
+// tiles or widths that 256-column tiles pad badly.
 //
-// LDS layout of a slab: 64 rows of 512 bytes, the 16-byte chunk c of row r at
+// LDS layout of a slab: 64 rows of 2 TS bytes, the 16-byte chunk c of row r at
 // chunk c ^ ((r & 3) << 2). A transposing read of half a wave touches 4
 // consecutive rows x 32 columns: 16 chunks, all in distinct banks. A 1 KB copy
-// moves two rows; LDS row 16 w + 2 p + b (wave w, piece p, b = lane / 32) holds
-// position 16 w + 8 b + p of the slab, so that a lane's 8 gathered rows are 8
-// consecutive table entries (two 16-byte loads per slab). The order of the
-// positions inside a K step is the same for both operands and changes nothing.
+// moves RP = 2 (4) rows; LDS row 16 w + RP p + b (wave w, piece p of NP = 8 (4),
+// b = lane * RP / 64) holds position 16 w + NP b + p of the slab, so that a lane's
+// NP gathered rows are consecutive table entries (16 or 8 bytes per half slab).
+// The order of the positions inside a K step is the same for both operands and
+// changes nothing.
 //
 // Gathered rows come from a table of byte offsets per window position; the
 // padding positions hold kWgradNoRow, past every buffer's end, and read as
@@ -41,15 +44,19 @@ namespace {
 // step, 18432 tokens 1739 -> 1477 us.
 //
 // GA: A is the gathered operand (dW2 = Gout^T act), else B (dW1 = dH^T x).
-template <bool GA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+template <bool GA, int TS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TS == 256 ? 1 : 2, TS == 256 ? 1 : 2)))
 void k_wgrad(const WgradArgs a) {
-    constexpr int BM = 256, BN = 256, WT = 128, FB = WT / 32;
-    constexpr int BK = 64, ROWB = 512;
-    constexpr int SLAB = BK * ROWB;  // 32 KB per operand and slab
+    static_assert(TS == 256 || TS == 128, "four waves of 128 x 128 or 64 x 64");
+    constexpr int BM = TS, BN = TS, WT = TS / 2, FB = WT / 32;
+    constexpr int BK = 64, ROWB = TS * 2;
+    constexpr int SLAB = BK * ROWB;  // 32 (16) KB per operand and slab
     constexpr int AST = 3, WST = 2;  // ring depths
     constexpr int WBASE = AST * SLAB;
-    constexpr int STG_WAVE = 32 * 256;  // epilogue staging bytes per wave
+    constexpr int STG_WAVE = SLAB / 4;  // epilogue staging bytes per wave
+    constexpr int NP = SLAB / 4096;     // 1 KB copies per wave, operand and slab
+    constexpr int RP = 16 / NP;         // LDS rows per copy
+    constexpr int LPR = kWave / RP;     // lanes (16-byte chunks) per row
     __shared__ __attribute__((aligned(1024))) uint8_t smem[AST * SLAB + WST * SLAB];
 
     const int n_n = (a.N + BN - 1) / BN;
@@ -106,12 +113,13 @@ void k_wgrad(const WgradArgs a) {
 
     // This lane's pieces: source position lpos + p, source chunk by the parity
     // of p (LDS row 16 w + 2 p + hb).
-    const int hb = lane >> 5;
-    const uint32_t lpos = 16 * wave + 8 * hb;
-    const uint32_t cofs[2] = {(uint32_t)((lane & 31) ^ (hb << 2)) * 16u, (uint32_t)((lane & 31) ^ ((2 + hb) << 2)) * 16u};
+    const int hb = lane / LPR;
+    const uint32_t lpos = 16 * wave + NP * hb;
+    const uint32_t cofs[2] = {(uint32_t)(lane % LPR ^ (hb << 2)) * 16u, (uint32_t)(lane % LPR ^ ((RP + hb) % 4 << 2)) * 16u};
     const uint32_t srow = GA ? brow : arow;  // row bytes of the sorted operand
     const uint32_t sbase[2] = {lpos * srow + cofs[0], lpos * srow + cofs[1]};
-    uint4 glo, ghi;  // byte offsets of pieces 0..3 and 4..7 of the next gathered slab
+    typedef uint32_t half_t __attribute__((ext_vector_type(NP / 2)));
+    half_t glo, ghi;  // byte offsets of the first and second half of the next gathered slab's pieces
 
     Tile tc = tile_at(lid);
     bool has_n = lid + wpx < lid_end;
@@ -131,7 +139,7 @@ void k_wgrad(const WgradArgs a) {
         if (s < tc.nk) q = tc.q0 + s * BK;
         else if (s - tc.nk < tn.nk) q = tn.q0 + (s - tc.nk) * BK;
         else q = tnn.q0;
-        return reinterpret_cast<const uint4*>(a.tab + q + lpos);
+        return reinterpret_cast<const half_t*>(a.tab + q + lpos);
     };
 
     f32x16_t acc[FB][FB];
@@ -153,27 +161,26 @@ void k_wgrad(const WgradArgs a) {
 #pragma unroll
     for (int i = 0; i < FB; ++i) {
         const uint32_t row = (uint32_t)(fk * 8 + r4) * ROWB + (uint32_t)(lane & 1) * 8u;
-        const uint32_t c = (uint32_t)(((i ^ r4) << 2) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1));
-        xoff[i] = base + row + (wm * 16 + c) * 16u;
-        woff[i] = base + WBASE + row + (wn * 16 + c) * 16u;
+        const uint32_t c = (uint32_t)(2 * ((lane >> 4) & 1) + ((lane & 3) >> 1));
+        xoff[i] = base + row + ((uint32_t)((wm * FB + i) ^ r4) * 4u + c) * 16u;
+        woff[i] = base + WBASE + row + ((uint32_t)((wn * FB + i) ^ r4) * 4u + c) * 16u;
     }
 
     // Piece L of an operand's slab: gathered from the table word, sorted at row
     // lpos + L of slab s.
     auto word = [&](auto LC) -> uint32_t {
         constexpr int L = decltype(LC)::value;
-        const uint4& v = L < 4 ? glo : ghi;
-        return L % 4 == 0 ? v.x : (L % 4 == 1 ? v.y : (L % 4 == 2 ? v.z : v.w));
+        return L < NP / 2 ? glo[L % (NP / 2)] : ghi[L % (NP / 2)];
     };
     auto copy_a = [&](auto LC, int stage, int s, __amdgpu_buffer_rsrc_t r) {
         constexpr int L = decltype(LC)::value;
         const uint32_t v = GA ? word(LC) + cofs[L & 1] : sbase[L & 1] + (uint32_t)(s * BK + L) * srow;
-        copy16_to_lds(r, v, 0, smem + stage * SLAB + (wave * 8 + L) * 1024);
+        copy16_to_lds(r, v, 0, smem + stage * SLAB + (wave * NP + L) * 1024);
     };
     auto copy_b = [&](auto LC, int stage, int s, __amdgpu_buffer_rsrc_t r) {
         constexpr int L = decltype(LC)::value;
         const uint32_t v = GA ? sbase[L & 1] + (uint32_t)(s * BK + L) * srow : word(LC) + cofs[L & 1];
-        copy16_to_lds(r, v, 0, smem + WBASE + stage * SLAB + (wave * 8 + L) * 1024);
+        copy16_to_lds(r, v, 0, smem + WBASE + stage * SLAB + (wave * NP + L) * 1024);
     };
 
     u32x2_t xf[2][FB][2], wf[2][FB][2];  // the two row halves of each fragment
@@ -204,8 +211,10 @@ void k_wgrad(const WgradArgs a) {
     auto frag = [](const u32x2_t(&h)[2]) {
         return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3));
     };
-    // One K step: 16 MFMAs on buffer CB, fragment q of the next K step after
-    // MFMA q (q < 8), copy q / 4 of the step's four after MFMA q when q % 4 == 1.
+    // One K step: 16 (4) MFMAs on buffer CB, fragment q of the next K step after
+    // MFMA q (q < 8 or 4), copy q / 4 (q / 2) of the step's four (two) after MFMA q
+    // when q % 4 (q % 2) == 1.
+    constexpr int CE = FB * FB / (NP / 2);  // MFMAs per copy
     auto kstep = [&](auto CBC, auto KSC, uint32_t rabase, uint32_t rwbase, auto&& copy) {
         constexpr int cb = decltype(CBC)::value;
         static_for<FB * FB>([&](auto QC) {
@@ -213,50 +222,53 @@ void k_wgrad(const WgradArgs a) {
             constexpr int j = q / FB, i = q % FB;
             acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(wf[cb][j]), frag(xf[cb][i]), acc[j][i], 0, 0, 0);
             if constexpr (q < 2 * FB) read_frag(std::integral_constant<int, cb ^ 1>{}, QC, KSC, rabase, rwbase);
-            if constexpr (q % 4 == 1) copy(std::integral_constant<int, q / 4>{});
+            if constexpr (q % CE == 1) copy(std::integral_constant<int, q / CE>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
     // Stores tile t, staged through A's ring slot `stslot` as k_gemm_pp does:
-    // 32 rows x 64 columns at a time, whole 256-byte row pieces out. Stacked
-    // gate and up gradients (a.h > 0: M = 2 ld rows, gate row r at r, up row r at
-    // ld + r) leave out the padding rows.
+    // 32 rows x 64 (32) columns at a time, whole 256-byte (128-byte) row pieces
+    // out. Stacked gate and up gradients (a.h > 0: M = 2 ld rows, gate row r at r,
+    // up row r at ld + r) leave out the padding rows.
     const int Mout = a.h > 0 ? 2 * a.h : a.M;
     auto epilogue = [&](const Tile& t, int stslot) {
+        constexpr int JB = TS == 256 ? 2 : 1;  // 32-column blocks per staged piece
+        constexpr int SROW = JB * 128, SCH = SROW / 16;  // bytes and 16-byte chunks of a staged row
+        constexpr int RPR = kWave / SCH, NR = 32 / RPR;  // rows per read, reads per piece
         const uint32_t stg = base + (uint32_t)stslot * SLAB + (uint32_t)wave * STG_WAVE;
-        const uint32_t wrow = stg + (uint32_t)fr * 256u;
-        const int sw = fr & 15;
+        const uint32_t wrow = stg + (uint32_t)(fr * SROW);
+        const int sw = fr & (SCH - 1);
         float* const ob = t.dest < 0 ? a.out + (size_t)t.e * Mout * a.N : a.partials + (size_t)t.dest * Mout * a.N;
 #pragma unroll
         for (int i = 0; i < FB; ++i)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < FB / JB; ++h) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
+                for (int jj = 0; jj < JB; ++jj)
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
-                        const int j = 2 * h + jj;
+                        const int j = JB * h + jj;
                         const u32x4_t v = {__float_as_uint(acc_read(acc[j][i][4 * g + 0])),
                                            __float_as_uint(acc_read(acc[j][i][4 * g + 1])),
                                            __float_as_uint(acc_read(acc[j][i][4 * g + 2])),
                                            __float_as_uint(acc_read(acc[j][i][4 * g + 3]))};
                         lds_write16_asm(wrow + ((uint32_t)((8 * jj + 2 * g + fk) ^ sw) << 4), v);
                     }
-                u32x4_t v[8];
+                u32x4_t v[NR];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int rr = (lane >> 4) + 4 * k;
-                    v[k] = lds_read16u_asm(stg + (uint32_t)rr * 256u + ((uint32_t)((lane & 15) ^ (rr & 15)) << 4));
+                for (int k = 0; k < NR; ++k) {
+                    const int rr = lane / SCH + RPR * k;
+                    v[k] = lds_read16u_asm(stg + (uint32_t)(rr * SROW) + ((uint32_t)(lane % SCH ^ (rr & (SCH - 1))) << 4));
                 }
                 wait_lgkmcnt0();
 #pragma unroll
-                for (int k = 0; k < 8; ++k) tie(v[k]);
-                const int col = t.n0 + wn * WT + h * 64;  // N is a multiple of 64
+                for (int k = 0; k < NR; ++k) tie(v[k]);
+                const int col = t.n0 + wn * WT + h * JB * 32;  // N is a multiple of 64
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    int m = t.m0 + wm * WT + i * 32 + (lane >> 4) + 4 * k;
+                for (int k = 0; k < NR; ++k) {
+                    int m = t.m0 + wm * WT + i * 32 + lane / SCH + RPR * k;
                     bool keep = m < a.M && col < a.N;
                     if (a.h > 0) {
                         const int ld = a.M / 2, up = m >= ld ? 1 : 0;
@@ -264,7 +276,7 @@ void k_wgrad(const WgradArgs a) {
                         keep = keep && r < a.h;
                         m = r + up * a.h;
                     }
-                    if (keep) store16_asm(ob + (size_t)m * a.N + col + (lane & 15) * 4, v[k]);
+                    if (keep) store16_asm(ob + (size_t)m * a.N + col + lane % SCH * 4, v[k]);
                 }
             }
     };
@@ -272,18 +284,18 @@ void k_wgrad(const WgradArgs a) {
     // Prologue: A slab 0, B slab 0, A slab 1, the first half of B slab 1.
     using std::integral_constant;
     auto first = [&](auto&& get) {
-        const uint4* const p = get;
+        const half_t* const p = get;
         glo = p[0];
         ghi = p[1];
     };
     first(table_at(0));
-    static_for<8>([&](auto LC) { copy_a(LC, 0, 0, ares_c); });
-    static_for<8>([&](auto LC) { copy_b(LC, 0, 0, bres_c); });
+    static_for<NP>([&](auto LC) { copy_a(LC, 0, 0, ares_c); });
+    static_for<NP>([&](auto LC) { copy_b(LC, 0, 0, bres_c); });
     first(table_at(1));
-    static_for<8>([&](auto LC) { copy_a(LC, 1, 1, ares_c); });
-    static_for<4>([&](auto LC) { copy_b(LC, 1, 1, bres_c); });
-    // GA: the next copies of A are slab 2's. Else B's: pieces 4..7 of slab 1,
-    // then pieces 0..3 of slab 2.
+    static_for<NP>([&](auto LC) { copy_a(LC, 1, 1, ares_c); });
+    static_for<NP / 2>([&](auto LC) { copy_b(LC, 1, 1, bres_c); });
+    // GA: the next copies of A are slab 2's. Else B's: the second half of slab
+    // 1's pieces, then the first half of slab 2's.
     glo = table_at(2)[0];
     if (GA) ghi = table_at(2)[1];
     // vmcnt(0) the compiler sees: it would otherwise count the table loads as
@@ -310,7 +322,7 @@ void k_wgrad(const WgradArgs a) {
             // K step 0: second half of B slab kt + 1.
             settle(integral_constant<int, 0>{});
             kstep(integral_constant<int, 0>{}, integral_constant<int, 1>{}, abase, wbase,
-                  [&](auto CC) { copy_b(integral_constant<int, 4 + decltype(CC)::value>{}, ws1, s1, br1); });
+                  [&](auto CC) { copy_b(integral_constant<int, NP / 2 + decltype(CC)::value>{}, ws1, s1, br1); });
             if (!GA) {
                 ghi = table_at(kt + 2)[1];
                 __builtin_amdgcn_sched_barrier(0);
@@ -321,16 +333,16 @@ void k_wgrad(const WgradArgs a) {
                   [&](auto CC) { copy_a(integral_constant<int, decltype(CC)::value>{}, as2, s2, ar2); });
             settle(integral_constant<int, 0>{});
             kstep(integral_constant<int, 0>{}, integral_constant<int, 3>{}, abase, wbase,
-                  [&](auto CC) { copy_a(integral_constant<int, 4 + decltype(CC)::value>{}, as2, s2, ar2); });
+                  [&](auto CC) { copy_a(integral_constant<int, NP / 2 + decltype(CC)::value>{}, as2, s2, ar2); });
             settle(integral_constant<int, 1>{});
             // Slab kt + 1 of both operands has landed for this wave: of the
-            // operations after its last copy at least the eight copies of A
+            // operations after its last copy at least the NP copies of A
             // slab kt + 2 may still be in flight. After the barrier it has for
             // every wave, and every wave is done reading slab kt.
-            wait_vmcnt<8>();
+            wait_vmcnt<NP>();
             barrier_no_fence();
             if (GA) {
-                const uint4* const p = table_at(kt + 3);
+                const half_t* const p = table_at(kt + 3);
                 glo = p[0];
                 ghi = p[1];
                 __builtin_amdgcn_sched_barrier(0);
@@ -383,12 +395,24 @@ void k_wgrad(const WgradArgs a) {
 
 }  // namespace
 
+// Tile: 256 x 256 (one workgroup per CU), or 128 x 128 (two per CU) where fewer
+// than 128 tiles of 256 x 256 would run, half of the CUs or more idle, or where
+// those would pad the widths by 1.6 times or more of what 128 x 128 tiles do
+// (320 columns: 512 against 384 both ways). Whole backward, 256 against 128
+// over 856 shapes: under 64 tiles 1.13 to 1.68 times as long, 64 to 127 1.01 to
+// 1.33, 128 to 191 0.91 to 1.16, more 0.91 to 1.23; padding ratios of 1.6 or
+// more 1.02 to 1.68 at any count. 8 experts of 2048 rows, d = 320, h = 448: each
+// product 78 -> 27 us; 8 of 8192 rows, d = h = 320: 141 -> 68 us.
 hipError_t launch_wgrad(const WgradArgs& a, bool gather_a, hipStream_t s) {
-    const long long tiles = (long long)a.items_max * ((a.M + 255) / 256) * ((a.N + 255) / 256);
-    const dim3 grid((unsigned)persistent_grid(tiles));
-    if (gather_a) hipLaunchKernelGGL(k_wgrad<true>, grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_wgrad<false>, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    auto tiles = [&](long long items, int ts) { return items * ((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts); };
+    auto go = [&](auto kern, int ts, int per_cu) -> hipError_t {
+        hipLaunchKernelGGL(kern, dim3((unsigned)persistent_grid(tiles(a.items_max, ts), per_cu)), dim3(256), 0, s, a);
+        return hipGetLastError();
+    };
+    // tiles(5, 256) * 4 >= tiles(8, 128): an area ratio of 1.6.
+    if (tiles(a.items_mean, 256) < 128 || tiles(5, 256) * 4 >= tiles(8, 128))
+        return gather_a ? go(k_wgrad<true, 128>, 128, 2) : go(k_wgrad<false, 128>, 128, 2);
+    return gather_a ? go(k_wgrad<true, 256>, 256, 1) : go(k_wgrad<false, 256>, 256, 1);
 }
 
 }  // namespace moe

@@ -1,7 +1,8 @@
 """Weight gradients from the row-major tensors: expert loads at the edges of
 the 64-row slabs and of the two-slab and 128-slab windows, and widths that are
-not multiples of the 256-column tiles (or of 64: SwiGLU), against the oracle
-with the backward's bounds (see test_gpu_backward)."""
+not multiples of the tiles (or of 64: SwiGLU), against the oracle with the
+backward's bounds (see test_gpu_backward). A few experts run on 128 x 128 tiles,
+the loads with 39 experts and more on 256 x 256 tiles."""
 
 import numpy as np
 import pytest
@@ -14,12 +15,14 @@ from workloads import bf16_bits_to_f32
 pytestmark = pytest.mark.gpu
 
 # Rows per expert; 8193 rows are cut into two work items.
-LOADS = {"edges": [0, 1, 63, 64, 65, 127, 128, 129, 0, 200, 1], "split": [8193, 0, 130]}
+EDGES = [0, 1, 63, 64, 65, 127, 128, 129, 0, 200, 1]
+LOADS = {"edges": EDGES, "split": [8193, 0, 130], "edges132": EDGES * 12, "split39": [8193, 0, 130] + [0, 1, 65] * 12}
 
 
 @pytest.mark.parametrize("d,h,swiglu,loads", [
     (320, 448, False, "edges"), (64, 64, False, "edges"), (512, 320, False, "split"), (576, 128, False, "edges"),
     (192, 33, True, "edges"), (320, 300, True, "edges"), (256, 65, True, "split"),
+    (576, 448, False, "edges132"), (704, 300, True, "edges132"), (576, 448, False, "split39"),
 ])
 def test_weight_gradient_windows(d, h, swiglu, loads):
     counts = np.array(LOADS[loads])
