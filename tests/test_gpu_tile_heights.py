@@ -3,7 +3,9 @@ an expert, forward and backward: 256-row tiles (a few experts to many, 180 to
 500 rows, widths that are rounded up to the 256-column tile), 128-row tiles
 (128 x 128 and 128 x 64, GELU and SwiGLU, widths that are odd multiples of 64 or
 no multiple of 64), 64-row tiles one row short of either, each with balanced and
-skewed loads (experts without rows among them).
+skewed loads (experts without rows among them). In the backward also 256-row
+tiles of more rows, with the widths rounded up to 256 columns on the persistent
+kernel (one pass well filled, or 800 tiles and more) and not rounded.
 
 Every row against torch in 64 bits, with the activation (and in the backward
 the pre-activation gradient) rounded to bf16 where the library rounds it. What
@@ -34,13 +36,17 @@ FORWARD = {
     "h64_narrow": (15000, 256, 128, 4, 256, "gelu"),
 }
 BACKWARD = {
-    "h256_rounded_640": (4000, 768, 32, 4, 640, "gelu"),
+    "h256_640": (4000, 768, 32, 4, 640, "gelu"),
     "h256_250rows": (2000, 1280, 32, 4, 1024, "gelu"),
     "h256_sw": (1440, 1536, 32, 4, 710, "swiglu"),
     "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
     "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
     "h128_sw": (7200, 512, 128, 4, 500, "swiglu"),
     "h128_sw_d576": (7200, 576, 128, 4, 500, "swiglu"),
+    "rounded_704": (7500, 704, 8, 2, 704, "gelu"),
+    "rounded_704_sw": (7500, 704, 8, 2, 300, "swiglu"),
+    "rounded_192_800tiles": (51200, 192, 8, 4, 192, "gelu"),
+    "tiled_448": (8192, 320, 8, 2, 448, "gelu"),
     "h64_8experts": (1400, 512, 8, 2, 512, "gelu"),
     "h64_sw_16experts": (1300, 1280, 16, 4, 854, "swiglu"),
 }
