@@ -13,7 +13,7 @@ namespace {
 //    rounded up to a multiple of 64 (the K slab) and to at least two slabs
 //    (the persistent kernel's pipeline holds two; an empty expert's positions
 //    all read as zeros, so its gradient comes out 0);
-//  - work items: each window cut into pieces of at most kWgradSlabs slabs,
+//  - work items: each window cut into pieces of at most `slabs` <= kWgradSlabs slabs,
 //    split evenly (sizes differ by at most one slab, and every piece keeps
 //    at least two slabs, as a window does), so that no tile runs
 //    much longer than the others under a skewed load. An expert with one
@@ -22,17 +22,18 @@ namespace {
 //    afterwards in that order;
 //  - rlist: the split experts {e, first partial block, pieces}.
 // wcount[0] = items, wcount[1] = split experts.
-__global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__ offsets, int E,
+// One thread per expert (the block is E rounded up to whole waves: 8 experts 7.8
+// -> 3.2 us against always 1024 threads).
+__global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__ offsets, int E, int slabs_max,
                                                     int32_t* __restrict__ koff, WgradItem* __restrict__ items,
                                                     TileDesc* __restrict__ rlist, int32_t* __restrict__ wcount) {
     __shared__ int32_t count_of[kWgradSlabs + 1], cursor[kWgradSlabs + 1];  // items, next position per length (slabs)
     __shared__ int4 wave_sum[1024 / kWave];
-    constexpr int CHUNK = kWgradSlabs * 64;
     static_assert(kMaxE <= 1024, "one expert per thread");
-    const int e = threadIdx.x, lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const int e = threadIdx.x, lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, waves = blockDim.x / kWave;
     const int start = e < E ? offsets[e] : 0, count = e < E ? offsets[e + 1] - start : 0;
     const int len = e < E ? max(128, (count + 63) / 64 * 64) : 0;
-    const int n = (len + CHUNK - 1) / CHUNK;
+    const int n = (len + slabs_max * 64 - 1) / (slabs_max * 64);
     for (int i = threadIdx.x; i <= kWgradSlabs; i += blockDim.x) count_of[i] = 0;
     // Running sums over the experts: window positions, items, partial blocks,
     // split experts. In a wave, then over the waves (256 experts: 19.7 -> 9.6 us
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__
     if (lane == kWave - 1) wave_sum[wave] = v;
     __syncthreads();
     int4 before = make_int4(v.x - own.x, v.y - own.y, v.z - own.z, v.w - own.w), all = make_int4(0, 0, 0, 0);
-    for (int w = 0; w < 1024 / kWave; ++w) {
+    for (int w = 0; w < waves; ++w) {
         const int4 u = wave_sum[w];
         if (w < wave) before = make_int4(before.x + u.x, before.y + u.y, before.z + u.z, before.w + u.w);
         all = make_int4(all.x + u.x, all.y + u.y, all.z + u.z, all.w + u.w);
@@ -77,11 +78,19 @@ __global__ __launch_bounds__(1024) void k_wgrad_plan(const int32_t* __restrict__
         if (n > extra) atomicAdd(&count_of[base], n - extra);
     }
     __syncthreads();
-    if (e <= kWgradSlabs) {
-        int run = 0;
-        for (int sz = kWgradSlabs; sz >= 0; --sz) run += sz > e ? count_of[sz] : 0;
-        cursor[e] = run;
-    }
+    // Wave 0: cursor[sz] = items longer than sz, a running sum from the longest.
+    if (wave == 0)
+        for (int hi = kWgradSlabs, longer = 0; hi >= 0; hi -= kWave) {
+            const int sz = hi - lane, own_c = sz >= 0 ? count_of[sz] : 0;
+            int c = own_c;
+#pragma unroll
+            for (int o = 1; o < kWave; o *= 2) {
+                const int u = __shfl_up(c, o);
+                if (lane >= o) c += u;
+            }
+            if (sz >= 0) cursor[sz] = longer + c - own_c;
+            longer += __shfl(c, kWave - 1);
+        }
     __syncthreads();
     if (e >= E) return;
     for (int c = 0, s0 = 0; c < n; ++c) {
@@ -183,9 +192,10 @@ __global__ __launch_bounds__(256) void k_slot_sum(const float* __restrict__ dxs,
 
 }  // namespace
 
-hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
-                             int32_t* wcount, hipStream_t s) {
-    hipLaunchKernelGGL(k_wgrad_plan, dim3(1), dim3(1024), 0, s, offsets, E, koff, items, rlist, wcount);
+hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int slabs, int32_t* koff, WgradItem* items,
+                             TileDesc* rlist, int32_t* wcount, hipStream_t s) {
+    hipLaunchKernelGGL(k_wgrad_plan, dim3(1), dim3((E + kWave - 1) / kWave * kWave), 0, s, offsets, E, slabs, koff,
+                       items, rlist, wcount);
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "moe_internal.h"
@@ -244,7 +245,15 @@ BackwardPlan plan_backward(const moe_desc_t& d) {
     b.koff = take(((size_t)d.E + 1) * 4);
     b.gtab = take((size_t)b.ld * 4);
     b.xtab = take((size_t)b.ld * 4);
-    b.items_max = d.E + (int32_t)(((size_t)b.ld / 64 + kWgradSlabs - 1) / kWgradSlabs);
+    // Windows are cut at 128 slabs. Few experts and narrow matrices give fewer
+    // 128 x 128 tiles than the CUs hold (two each) with one item per expert: there
+    // the cut is shorter, down to 16 slabs, to spread the rows (the partial blocks
+    // stay under 512 tiles of 64 KB and one per expert). 8 experts of 8192 rows, d =
+    // h = 320: each product 98 -> 43 us, its sum 5 -> 12; of 2048 rows, 320 x 448:
+    // 40 -> 16 and 5 -> 5.
+    const int64_t tiles = (int64_t)((d.d + 127) / 128) * ((b.hh + 127) / 128), all = (int64_t)(TK / 64) + d.E;
+    b.slabs = d.E * tiles >= 512 ? kWgradSlabs : (int32_t)std::min<int64_t>(std::max<int64_t>(all * tiles / 512, 16), kWgradSlabs);
+    b.items_max = d.E + (int32_t)(((size_t)b.ld / 64 + b.slabs - 1) / b.slabs);
     b.items = take((size_t)b.items_max * sizeof(WgradItem));
     b.rlist = take((size_t)d.E * sizeof(TileDesc));
     b.wcount = take(16);
@@ -424,7 +433,7 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     TileDesc* rlist = region<TileDesc>(ws, b.rlist);
     int32_t* wcount = region<int32_t>(ws, b.wcount);
     float* partials = region<float>(ws, b.partials);
-    HIP_CHECK(launch_wgrad_plan(offsets, d.E, koff, items, rlist, wcount, s), "weight-gradient plan");
+    HIP_CHECK(launch_wgrad_plan(offsets, d.E, b.slabs, koff, items, rlist, wcount, s), "weight-gradient plan");
     HIP_CHECK(launch_wgrad_rows(sorted_slots, offsets, koff, d.E, d.K, (uint32_t)d.d * 2, gtab, xtab, b.ld, s),
               "weight-gradient rows");
 

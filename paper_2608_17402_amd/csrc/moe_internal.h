@@ -134,6 +134,7 @@ struct BackwardPlan {
     size_t partials;         // [items_max, d, hw] fp32 partial sums of split experts
     int32_t hh, hw;
     int32_t ld;              // bound on the window positions: T*K + 128 E, rounded up to 64
+    int32_t slabs;           // longest work item, in 64-row slabs (4 .. kWgradSlabs)
     int32_t items_max;       // bound on the work items (and on the partial blocks)
     size_t total;
 };
@@ -219,8 +220,8 @@ struct WgradArgs {
 hipError_t launch_wgrad(const WgradArgs& a, bool gather_a, hipStream_t s);
 // Workgroups of a persistent kernel with at most tile_bound tiles, per_cu of them on a CU.
 int persistent_grid(long long tile_bound, int per_cu = 1);
-hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int32_t* koff, WgradItem* items, TileDesc* rlist,
-                             int32_t* wcount, hipStream_t s);
+hipError_t launch_wgrad_plan(const int32_t* offsets, int E, int slabs, int32_t* koff, WgradItem* items,
+                             TileDesc* rlist, int32_t* wcount, hipStream_t s);
 hipError_t launch_wgrad_reduce(const float* partials, const TileDesc* rlist, const int32_t* wcount, int E,
                                size_t mn, float* out, hipStream_t s);
 // Byte offsets of every window position's row in the slot rows (slot *

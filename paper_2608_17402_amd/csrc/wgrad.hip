@@ -402,7 +402,8 @@ void k_wgrad(const WgradArgs a) {
 // over 856 shapes: under 64 tiles 1.13 to 1.68 times as long, 64 to 127 1.01 to
 // 1.33, 128 to 191 0.91 to 1.16, more 0.91 to 1.23; padding ratios of 1.6 or
 // more 1.02 to 1.68 at any count. 8 experts of 2048 rows, d = 320, h = 448: each
-// product 78 -> 27 us; 8 of 8192 rows, d = h = 320: 141 -> 68 us.
+// product 76 -> 40 us; 8 of 8192 rows, d = h = 320: 139 -> 98 us (with one item
+// per expert; BackwardPlan::slabs shortens them).
 hipError_t launch_wgrad(const WgradArgs& a, bool gather_a, hipStream_t s) {
     auto tiles = [&](long long items, int ts) { return items * ((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts); };
     auto go = [&](auto kern, int ts, int per_cu) -> hipError_t {
