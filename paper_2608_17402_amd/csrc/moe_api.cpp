@@ -368,7 +368,7 @@ static moe_status_t enqueue_shared_mlp(const moe_desc_t& d, const WorkspacePlan&
     if (fused) *fused = false;
     const bool swiglu = d.flags & MOE_FLAG_SWIGLU;
     const int32_t ldh = act_stride(d, d.h_shared);
-    int bm = gemm_dense_bm(d.dtype, d.T, ldh < d.d ? ldh : d.d);
+    int bm = gemm_dense_bm(d);
     if (swiglu && d.d < 128) bm = 64;  // 256-row SwiGLU tiles need two or more K slabs
     GemmArgs g{};
     g.A = x;

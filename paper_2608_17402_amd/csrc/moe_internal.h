@@ -147,8 +147,8 @@ int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows, bool backward);
 inline int32_t act_stride(const moe_desc_t& d, int32_t h) {
     return (d.flags & MOE_FLAG_SWIGLU) ? (h + 63) / 64 * 64 : h;
 }
-// M-tile height of a dense GEMM of `rows` rows and `n` output columns.
-int gemm_dense_bm(int32_t dtype, int64_t rows, int32_t n);
+// M-tile height of the shared expert's two dense GEMMs.
+int gemm_dense_bm(const moe_desc_t& d);
 
 // ---- launchers (each returns the first HIP error, hipSuccess otherwise)
 // Exact routing: every logit by the matrix-core chain into logits [T, ld]
