@@ -1275,18 +1275,26 @@ bool router_small_batch(const moe_desc_t& d) { return d.T < 256 * 64; }
 // Every logit by the matrix-core chain, or only the candidates of a bf16
 // pre-pass? The chain costs 2 T E d flop at 100 to 115 TFLOP/s; the pre-pass
 // runs at the bf16 rate and its repair costs about eight chains per token plus
-// five launches. Measured (us, exact against repair): E = 64 wins at every T
-// (768 wide: 13 / 17 at 5 tokens, 42 / 59 at 32768, 73 / 89 at 65536); with
+// three more launches. Measured (us, exact against repair): E = 64 wins at every
+// T (768 wide: 13 / 17 at 5 tokens, 42 / 59 at 32768, 73 / 89 at 65536); with
 // 64 < E <= 256 up to the large-batch chain kernel (E = 128, d = 1024: 52 / 138
 // at 16383 tokens, but 68 / 68 at 18432 and 163 / 113 at 65536; E = 256, d =
-// 1536: 125 / 187 at 16383, 151 / 116 at 18432); with more experts only where
-// the interval test fails: its width grows with d |x| |w|, and past d = 2048
-// most experts become candidates and most tokens go through the overflow
-// queue (d = 4096, E = 256, weights of deviation 0.02: 94 / 520 us at 1025
-// tokens, 1.1 / 37 ms at 65536; E = 300, d = 1024: 34 / 31 at 1025 tokens).
+// 1536: 125 / 187 at 16383, 151 / 116 at 18432); else only where the interval
+// test fails. Its width grows with d |x| |w|: past some d most experts become
+// candidates and most tokens go through the overflow queue, which costs up to
+// 130 times the chain. Where that begins depends on the data, which is not known
+// here; the lines are those of normal weights of deviation 0.02 and unit x. Large
+// batches, E = 256: 384 / 261 at d = 2112 and 40000 tokens, 2560 0.77, 2688 1.0,
+// 3072 582 / 1526; E = 512: 860 / 558 at 2112, 2432 0.97 to 1.18, 2688 2.3; E =
+// 1024: 1656 / 1261 at 2112, 2240 1.2. Small ones (more than 256 experts): 2000
+// tokens, E = 1024, d = 2112 118 / 424 (K = 4: 102 / 64), 300 tokens, E = 300, d =
+// 4096 49 / 638; E = 300, d = 1024, 1025 tokens 34 / 31. Smaller weights would
+// carry the repair further (deviation 0.002, 40000 tokens, d = 3072, E = 256 548 /
+// 370, E = 1024 2311 / 1069): the bounded cost is preferred.
 bool router_exact(const moe_desc_t& d) {
-    return d.dtype != MOE_BF16 || (d.flags & MOE_FLAG_EXACT_ROUTER) || d.d > 2048 || d.E <= 64 ||
-           (d.E <= 256 && router_small_batch(d));
+    if (d.dtype != MOE_BF16 || (d.flags & MOE_FLAG_EXACT_ROUTER) || d.E <= 64) return true;
+    if (router_small_batch(d)) return d.E <= 256 || d.d > 2048;
+    return d.d > (d.E <= 256 ? 2624 : (d.E <= 512 ? 2368 : 2176));
 }
 
 hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, int ld, int nsplit, const void* x,
