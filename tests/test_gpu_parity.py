@@ -54,8 +54,9 @@ def test_route_bit_exact(small):
 
 
 def test_route_exact_flag_agrees(small):
-    # The all-exact router and the MFMA pre-pass with exact repair must give
-    # the same routing, bit for bit.
+    # The all-exact flag is accepted and gives the same routing, bit for bit
+    # (the layers here compute every logit exactly without it too; the pre-pass
+    # against the exact router: test_gpu_router_repair).
     cfg, inp, lay, _, ref_idx, ref_gate = small
     d2 = desc_for(cfg, flags=binding.MOE_FLAG_EXACT_ROUTER)
     idx = torch.empty(cfg.T, cfg.K, dtype=torch.int32, device="cuda")
@@ -68,12 +69,9 @@ def test_route_exact_flag_agrees(small):
 @pytest.mark.parametrize("T,d,E,K", [(1, 64, 8, 2), (130, 2048, 256, 8), (77, 4096, 200, 6), (300, 4096, 64, 8),
                                      (513, 1344, 128, 1), (9001, 256, 128, 8), (16383, 192, 256, 4)])
 def test_route_small_batch_widths(T, d, E, K):
-    # Small batches route in one launch after the logits GEMM, the weight
-    # rows streaming through LDS in 128-column chunks (d = 1344 ends on a
-    # 64-column chunk); up to d = 4096 the x rows and three chunk buffers
-    # share the LDS. From 8192 tokens the logits GEMM runs unsplit, and 16383
-    # is the largest batch on this path. Bit-exact against the oracle and the
-    # all-exact path.
+    # Small batches with at most 256 experts, every logit by the matrix-core
+    # chain: narrow and wide rows, 16 x 16 and 32 x 32 wave tiles, up to 16383
+    # tokens, the largest batch on this path. Bit-exact against the oracle.
     from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 
     rng = np.random.default_rng(T * 7 + d + E + K)
@@ -81,15 +79,14 @@ def test_route_small_batch_widths(T, d, E, K):
     wr = f32_to_bf16_bits((rng.standard_normal((E, d)) * 0.02).astype(np.float32))
     bias = rng.uniform(-0.02, 0.02, E).astype(np.float32)
     ref_idx, ref_gate = oracle.route(bf16_bits_to_f32(x), bf16_bits_to_f32(wr), bias, K)
-    for flags in (0, binding.MOE_FLAG_EXACT_ROUTER):
-        desc = binding.make_desc(T, d, E, K, 64, flags=flags)
-        ws = binding.alloc_workspace(desc)
-        idx = torch.empty(T, K, dtype=torch.int32, device="cuda")
-        gate = torch.empty(T, K, dtype=torch.float32, device="cuda")
-        binding.moe_route(desc, dev(x), dev(wr), dev(bias), idx, gate, ws)
-        torch.cuda.synchronize()
-        assert np.array_equal(host(idx), ref_idx), flags
-        assert np.array_equal(host(gate), ref_gate), flags
+    desc = binding.make_desc(T, d, E, K, 64)
+    ws = binding.alloc_workspace(desc)
+    idx = torch.empty(T, K, dtype=torch.int32, device="cuda")
+    gate = torch.empty(T, K, dtype=torch.float32, device="cuda")
+    binding.moe_route(desc, dev(x), dev(wr), dev(bias), idx, gate, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(idx), ref_idx)
+    assert np.array_equal(host(gate), ref_gate)
 
 
 def _route_case(rng):
@@ -104,10 +101,9 @@ def _route_case(rng):
 
 @pytest.mark.parametrize("seed", range(40))
 def test_route_random_small_batches(seed):
-    # Seeded random shapes of the small-batch router (one launch after the
-    # logits GEMM; overflowing tokens routed in full by their block): widths
-    # 64 to 2048, E 1 to 256, K up to 8, some experts in groups of identical
-    # rows, with and without a bias. Bit-exact against the oracle.
+    # Seeded random shapes of the small-batch router (every logit exactly):
+    # widths 64 to 2048, E 1 to 256, K up to 8, some experts in groups of
+    # identical rows, with and without a bias. Bit-exact against the oracle.
     from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 
     rng = np.random.default_rng(5000 + seed)
@@ -130,10 +126,9 @@ def test_route_random_small_batches(seed):
 
 
 @pytest.mark.parametrize("dup", [1, 16, 128])
-def test_route_near_ties_take_exact_fallback(dup):
-    # Groups of `dup` identical router rows tie exactly for every token; with
-    # dup = 128 every expert is a candidate, more than the repair keeps, so
-    # every token goes through the exact all-experts kernel.
+def test_route_ties(dup):
+    # Groups of `dup` identical router rows tie exactly for every token, up to
+    # all 128 experts (the repair's overflow by ties: test_gpu_router_repair).
     T, d, E, K = 300, 256, 128, 8
     rng = np.random.default_rng(dup)
     from workloads import bf16_bits_to_f32, f32_to_bf16_bits
@@ -156,9 +151,10 @@ def test_route_near_ties_take_exact_fallback(dup):
 
 @pytest.mark.parametrize("E,K", [(1, 1), (5, 3), (31, 7), (63, 8), (65, 8), (100, 16), (128, 8), (200, 4),
                                  (300, 8), (1000, 12)])
-def test_route_fast_path_any_expert_count(E, K):
-    # The MFMA pre-pass pads the logits to a multiple of 64 columns; routing
-    # must still equal the oracle's and the all-exact path's, bit for bit.
+def test_route_any_expert_count(E, K):
+    # The logits are padded to a multiple of 64 columns; routing must still
+    # equal the oracle's, bit for bit, and (more than 256 experts: the bf16
+    # pre-pass and its repair) the all-exact path's.
     from workloads import bf16_bits_to_f32, f32_to_bf16_bits
 
     T, d = 1500, 320
@@ -167,7 +163,7 @@ def test_route_fast_path_any_expert_count(E, K):
     wr = f32_to_bf16_bits((rng.standard_normal((E, d)) * 0.05).astype(np.float32))
     bias = rng.uniform(-0.05, 0.05, E).astype(np.float32)
     ref_idx, ref_gate = oracle.route(bf16_bits_to_f32(x), bf16_bits_to_f32(wr), bias, K)
-    for flags in (0, binding.MOE_FLAG_EXACT_ROUTER):
+    for flags in (0, binding.MOE_FLAG_EXACT_ROUTER) if E > 256 else (0,):
         desc = binding.make_desc(T, d, E, K, 64, flags=flags)
         ws = binding.alloc_workspace(desc)
         idx = torch.empty(T, K, dtype=torch.int32, device="cuda")
@@ -295,8 +291,7 @@ EDGE = {
     "k16_e1024": dict(T=50, d=64, E=1024, K=16, h=64, hs=0, dtype="bf16"),
     "f32_ragged": dict(T=131, d=192, E=5, K=3, h=320, hs=128, dtype="f32"),
     "wide_h_odd_tiles": dict(T=257, d=320, E=6, K=2, h=448, hs=192, dtype="bf16"),
-    # the descriptor's largest widths: d = h = h_s = 8192 (128 K slabs; the
-    # small-batch router stages 4 x 16 KB x rows in LDS). Weights of std
+    # the descriptor's largest widths: d = h = h_s = 8192 (128 K slabs). Weights of std
     # 0.02 sqrt(1536 / 8192) keep pre-activations and outputs at the ViT-G
     # layer's magnitudes, where the bf16 bounds are stated (with std 0.02 the
     # outputs reach 8, whose bf16 spacing alone exceeds 2e-2).
