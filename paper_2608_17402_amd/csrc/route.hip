@@ -304,19 +304,31 @@ struct ChainFrag {
     __device__ static uint32_t selector(int q) {  // bytes of column q's half into the high half, 0 below
         return (q & 1) ? 0x03020c0cu : 0x01000c0cu;
     }
-    __device__ static void read(uint32_t (&w)[N], uint32_t addr) {
+    // Reads of whole chunks fill a vector, which is split into words only after
+    // the wait: a copy of a word before it could carry the register's old value.
+    static constexpr bool VEC = PERM || (!BF16 && N == 2);
+    typedef uint32_t vec_t __attribute__((ext_vector_type(PERM ? 4 : 2)));
+    __device__ static void read(vec_t& v, uint32_t (&w)[N], uint32_t addr) {
         if constexpr (PERM) {
-            const u32x4_t v = lds_read16u_asm(addr);
-            w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+            v = lds_read16u_asm(addr);
+        } else if constexpr (VEC) {
+            lds_read2_asm(v, addr);
         } else if constexpr (BF16) {
             asm volatile("ds_read_u16_d16_hi %0, %1" : "+v"(w[0]) : "v"(addr));
             asm volatile("ds_read_u16_d16_hi %0, %1 offset:8" : "+v"(w[1]) : "v"(addr));
-        } else if constexpr (N == 2) {
-            u32x2_t v;
-            lds_read2_asm(v, addr);
-            w[0] = v.x, w[1] = v.y;
         } else {
             asm volatile("ds_read_b32 %0, %1" : "=v"(w[0]) : "v"(addr));
+        }
+    }
+    // The words of a read that has been waited for.
+    __device__ static void landed(vec_t& v, uint32_t (&w)[N]) {
+        if constexpr (VEC) {
+            tie(v);
+#pragma unroll
+            for (int m = 0; m < N; ++m) w[m] = v[m];
+        } else {
+#pragma unroll
+            for (int m = 0; m < N; ++m) tie(w[m]);
         }
     }
 };
@@ -378,11 +390,12 @@ __global__ __launch_bounds__(256) void k_router_logits(const TIn* __restrict__ x
     uint32_t sel = Frag::selector(q);
     asm volatile("" : "+v"(sel));
     uint32_t xf[2][CH][NF] = {}, wf[2][CH][NF] = {};
+    typename Frag::vec_t xv[2][CH], wv[2][CH];
     auto read_chunk = [&](int slot, auto HC, int c) {
         constexpr int h = decltype(HC)::value;
         const uint32_t o = (uint32_t)slot * SLAB + (uint32_t)(((CH * h + c) ^ sw) << 4);
-        Frag::read(xf[h][c], xo + o);
-        Frag::read(wf[h][c], eo + o);
+        Frag::read(xv[h][c], xf[h][c], xo + o);
+        Frag::read(wv[h][c], wf[h][c], eo + o);
     };
     // Half h's words have landed; widen them (PERM). All of it before the
     // half's first MFMA: a vector operation between two dependent MFMAs costs
@@ -392,16 +405,16 @@ __global__ __launch_bounds__(256) void k_router_logits(const TIn* __restrict__ x
         constexpr int h = decltype(HC)::value;
         wait_lgkmcnt0();
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c) {
+            Frag::landed(wv[h][c], wf[h][c]);
+            Frag::landed(xv[h][c], xf[h][c]);
+            if constexpr (Frag::PERM)
 #pragma unroll
-            for (int m = 0; m < NF; ++m) {
-                tie(wf[h][c][m]);
-                tie(xf[h][c][m]);
-                if constexpr (Frag::PERM) {
+                for (int m = 0; m < NF; ++m) {
                     wf[h][c][m] = __builtin_amdgcn_perm(0u, wf[h][c][m], sel);
                     xf[h][c][m] = __builtin_amdgcn_perm(0u, xf[h][c][m], sel);
                 }
-            }
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     typedef float acc_t __attribute__((ext_vector_type(NA)));
