@@ -1909,7 +1909,8 @@ hipError_t launch_128(const GemmArgs& a, hipStream_t s) {
 
 // Tile shapes. Large groups (M-tiles of 256 token rows): 256 x 256 on the
 // persistent kernel when N allows and K spans at least two slabs (the paced
-// one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Between (gemm_tile_bm) 128-row tiles. Small
+// one-tile kernel for one slab), else 256 x 128 or 256 x 64 tiled. Between
+// (gemm_tile_bm, gemm_dense_bm) 128 x 128 or 128 x 64. Small
 // groups (M-tiles of 64 rows, the weight-read-bound regime where an expert
 // sees a few dozen tokens): 64 x 128 or 64 x 64 with three slabs in the ring
 // and several workgroups per CU, to keep many weight loads in flight.
@@ -2150,8 +2151,8 @@ int gemm_dense_bm(const moe_desc_t& d) {
 }
 
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim) {
-    // The persistent 256 x 256 kernel with its combine epilogue, or the
-    // 64-row tiled kernel with its own (K <= 8 either way).
+    // The persistent 256 x 256 kernel with its combine epilogue, or the tiled
+    // kernel's 128- or 64-row tiles with theirs (K <= 8 either way).
     if (d.dtype != MOE_BF16 || d.K > kMaxCombineK) return false;
     return (bm == 256 && n % 256 == 0 && kdim >= 128) || (bm <= 128 && n % 64 == 0);
 }

@@ -14,12 +14,6 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ bf16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (bf16_t)(u >> 16);
-}
-
 // GELU for the bf16 path: GELU(x) = x Phi(x) with the normal CDF Phi taken
 // as Sigmoid(s(x)), s(x) = x (a0 + a1 x^2 + a2 x^4) evaluated on x clamped
 // to [-8, 8]. The coefficients minimise the largest absolute error of the
@@ -43,7 +37,6 @@ __device__ __forceinline__ float silu_as(float v) {
     return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * -1.44269504f));
 }
 
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
@@ -62,10 +55,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int N>
-__device__ __forceinline__ void wait_lgkmcnt() {
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
-}
 __device__ __forceinline__ void wait_lgkmcnt0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Workgroup barrier without the memory fence of __syncthreads (which would
@@ -154,9 +143,6 @@ __device__ __forceinline__ u32x4_t lds_read16u_asm(uint32_t addr) {
     return r;
 }
 __device__ __forceinline__ void tie(u32x4_t& v) { asm volatile("" : "+v"(v)); }
-__device__ __forceinline__ void lds_read_u16_asm(uint32_t& r, uint32_t addr) {
-    asm volatile("ds_read_u16 %0, %1" : "=v"(r) : "v"(addr));
-}
 __device__ __forceinline__ void tie(uint32_t& v) { asm volatile("" : "+v"(v)); }
 // Transposing 8-byte LDS read (ds_read_b64_tr_b16, CDNA4). Within each group
 // of 16 lanes, lane r names 4 consecutive 16-bit values M[r][0..3]; lane i

@@ -90,7 +90,7 @@ struct GemmArgs {
     int32_t b_half;            // K-major weights of two stacked matrices: K columns of each half (act_n of them
                                // with a weight row); 0 = one matrix
     int32_t act_n;             // EPI_SWIGLU_STORE: activation width h (valid columns)
-    int32_t act_ld;            // EPI_SWIGLU_STORE: activation row stride (h rounded up to 128)
+    int32_t act_ld;            // EPI_SWIGLU_STORE: activation row stride (h rounded up to 64)
     const float* gate;         // EPI_COMBINE: gates [rows, route_k]
     const void* eo;            // EPI_COMBINE: expert outputs [rows * route_k, N] in slot order
     float lambda;              // EPI_COMBINE: shared-expert weight
@@ -229,9 +229,6 @@ hipError_t launch_wgrad_reduce(const float* partials, const TileDesc* rlist, con
 hipError_t launch_wgrad_rows(const int32_t* sorted_slots, const int32_t* offsets, const int32_t* koff, int E, int K,
                              uint32_t row_bytes, uint32_t* gtab, uint32_t* xtab, int ld, hipStream_t s);
 hipError_t launch_slot_sum(const float* dxs, int T, int K, int d, void* dx, hipStream_t s);
-// Zeroes the windows of experts with no rows in a slab-major operand [ld / 64][C][64].
-hipError_t launch_zero_empty_windows(void* out, int C, const int32_t* offsets, const int32_t* koff, int E,
-                                     hipStream_t s);
 hipError_t launch_bias_update(int32_t E, const int32_t* counts, float* bias, float alpha, int32_t rule,
                               hipStream_t s);
 hipError_t launch_combine(const moe_desc_t& d, const void* expert_out, const float* gate,

@@ -188,24 +188,17 @@ __device__ __forceinline__ float sigmoid_fast(float s) {
 // Upper bound of the 2-norm of every row of a [rows, d] bf16 matrix (fp32 sum
 // of squares, inflated to cover its rounding). One wave per row. Block 0 also
 // clears the overflow counter used by the repair kernel.
-__global__ __launch_bounds__(256) void k_row_norms(const bf16_t* __restrict__ a, int rows_a,
-                                                   float* __restrict__ out_a, const bf16_t* __restrict__ b,
-                                                   int rows_b, float* __restrict__ out_b, int d,
-                                                   int32_t* __restrict__ clear, float* __restrict__ a32) {
-    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
+__global__ __launch_bounds__(256) void k_row_norms(const bf16_t* __restrict__ a, int rows, float* __restrict__ out,
+                                                   int d, int32_t* __restrict__ clear, float* __restrict__ a32) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     const int lane = threadIdx.x & (kWave - 1);
-    // One wave per row: the rows of a, then (from the next block on) those of b.
-    const int wpb = blockDim.x / kWave;
-    const int blocks_a = (rows_a + wpb - 1) / wpb;
-    const bool second = (int)blockIdx.x >= blocks_a;
-    const int row = ((int)blockIdx.x - (second ? blocks_a : 0)) * wpb + threadIdx.x / kWave;
-    if (row >= (second ? rows_b : rows_a)) return;
-    const bf16_t* p = (second ? b : a) + (size_t)row * d;
-    float* out = second ? out_b : out_a;
+    const int row = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (row >= rows) return;
+    const bf16_t* p = a + (size_t)row * d;
     float acc = 0.0f;
     // a32 (optional): the rows of a widened to fp32 (exact), for the
     // small-batch chain kernel.
-    float* const r32 = (a32 && !second) ? a32 + (size_t)row * d : nullptr;
+    float* const r32 = a32 ? a32 + (size_t)row * d : nullptr;
     for (int i = lane * 8; i < d; i += kWave * 8) {
         float v[8];
         load8(p + i, v);
@@ -363,7 +356,7 @@ __global__ __launch_bounds__(256) void k_router_logits(const TIn* __restrict__ x
     const uint32_t rowb = (uint32_t)d * sizeof(TIn);
     const __amdgpu_buffer_rsrc_t xres = make_rsrc(x, (uint32_t)T * rowb);
     const __amdgpu_buffer_rsrc_t wres = make_rsrc(wr, (uint32_t)E * rowb);
-    // Copy piece i of this wave: 8 rows, tokens first; token rows past T repeat
+    // Copy piece i of this wave: RPP rows (8, or 4 of 256 bytes), tokens first; token rows past T repeat
     // the last one (not stored), expert rows past E read as zeros.
     auto swz = [](int r) { return CPR == 8 ? (r >> 1) & 7 : r & 15; };
     uint32_t off[P];
@@ -1316,30 +1309,33 @@ hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, i
                                      int32_t* topk_idx, float* topk_gate, hipStream_t s) {
     const bf16_t* xb = static_cast<const bf16_t*>(x);
     const bf16_t* wb = static_cast<const bf16_t*>(w_router);
-    if (nsplit < 1 || nsplit > 8) return hipErrorInvalidValue;  // the candidate kernels add at most 8 parts
+    // The candidate kernels add at most 8 parts, those of up to 256 experts none.
+    if (nsplit < 1 || nsplit > 8 || (d.E <= 256 && nsplit > 1)) return hipErrorInvalidValue;
     const bool small = router_small_batch(d);
     // Weight-row norms (the token norms are formed in the candidate kernel);
     // for small batches also the fp32 copy of the weights the chains read.
-    hipLaunchKernelGGL(k_row_norms, dim3((d.E + 3) / 4), dim3(256), 0, s, wb, d.E, wnorm, nullptr, 0, nullptr, d.d,
-                       ovf_count, small ? wr32 : nullptr);
+    hipLaunchKernelGGL(k_row_norms, dim3((d.E + 3) / 4), dim3(256), 0, s, wb, d.E, wnorm, d.d, ovf_count,
+                       small ? wr32 : nullptr);
     const size_t sstride = (size_t)d.T * ld;
     const float cst = router_fast_bound_constant(d.d);
     const int ns = router_cand_slots(d.K);
-    // Candidates: 16 lanes per token (64 for more than 256 experts); blocks
-    // of one wave for small batches, so that every CU gets work.
-    const int cand_threads = d.T >= 16384 ? 256 : kWave;
-#define MOE_CAND(LPAv, PERv, NSv)                                                                           \
-    hipLaunchKernelGGL((nsplit > 1 ? k_router_cand<LPAv, PERv, NSv, true> : k_router_cand<LPAv, PERv, NSv, false>), \
-                       dim3((d.T + cand_threads / LPAv - 1) / (cand_threads / LPAv)), dim3(cand_threads), 0, s, \
-                       s_fast, xb, xnorm2, d.d, wnorm, bias, d.T, d.E, ld, d.K, cst, cand, ncand, ovf_count,    \
-                       ovf_list, nsplit, sstride)
-    // E / LPA experts per lane (at least 4), so that every lane of a token
-    // holds experts and L is taken over all of them.
-    if (d.E <= 128) { if (ns == 16) MOE_CAND(16, 8, 16); else MOE_CAND(16, 8, 32); }
-    else if (d.E <= 256) { if (ns == 16) MOE_CAND(16, 16, 16); else MOE_CAND(16, 16, 32); }
-    else if (d.E <= 512) { if (ns == 16) MOE_CAND(64, 8, 16); else MOE_CAND(64, 8, 32); }
-    else { if (ns == 16) MOE_CAND(64, 16, 16); else MOE_CAND(64, 16, 32); }
-#undef MOE_CAND
+    // Candidates: 16 lanes per token, or 64 for more than 256 experts; there
+    // blocks of one wave for small batches, so that every CU gets work (with
+    // fewer experts only large batches come here, with unsplit logits).
+    auto cands = [&](auto kern, int lpa, int threads) {
+        const int tpb = threads / lpa;
+        hipLaunchKernelGGL(kern, dim3((d.T + tpb - 1) / tpb), dim3(threads), 0, s, s_fast, xb, xnorm2, d.d, wnorm, bias,
+                           d.T, d.E, ld, d.K, cst, cand, ncand, ovf_count, ovf_list, nsplit, sstride);
+    };
+    // E / LPA experts per lane (8 or 16), so that every lane of a token holds
+    // experts and L is taken over all of them.
+    auto wide = [&](auto split, auto whole) { nsplit > 1 ? cands(split, 64, kWave) : cands(whole, 64, small ? kWave : 256); };
+    if (d.E <= 128) ns == 16 ? cands(k_router_cand<16, 8, 16, false>, 16, 256) : cands(k_router_cand<16, 8, 32, false>, 16, 256);
+    else if (d.E <= 256) ns == 16 ? cands(k_router_cand<16, 16, 16, false>, 16, 256) : cands(k_router_cand<16, 16, 32, false>, 16, 256);
+    else if (d.E <= 512) ns == 16 ? wide(k_router_cand<64, 8, 16, true>, k_router_cand<64, 8, 16, false>)
+                                  : wide(k_router_cand<64, 8, 32, true>, k_router_cand<64, 8, 32, false>);
+    else ns == 16 ? wide(k_router_cand<64, 16, 16, true>, k_router_cand<64, 16, 16, false>)
+                  : wide(k_router_cand<64, 16, 32, true>, k_router_cand<64, 16, 32, false>);
     // Exact chains: 256 (or 128) tokens per block of 1024 threads while that
     // still gives a block per CU, then 64 tokens per block, then (small
     // batches) one wave per 4 (or 2) tokens reading weights directly.
@@ -1367,11 +1363,6 @@ hipError_t launch_router_fast_finish(const moe_desc_t& d, const float* s_fast, i
         const int chain_blocks = (d.T + tpb - 1) / tpb;
         const dim3 grid(chain_blocks + 64);
         auto launch = [&](auto kern) -> hipError_t {
-            if (shm > 65536) {  // x rows of d > 4096 in LDS
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-                if (e != hipSuccess) return e;
-            }
             hipLaunchKernelGGL(kern, grid, dim3(kWave), shm, s, xb, wr32, wb, bias, cand, ncand, d.T, d.d, d.E, d.K,
                                topk_idx, topk_gate, chain_blocks, ovf_count, ovf_list);
             return hipGetLastError();
