@@ -1946,21 +1946,21 @@ hipError_t dispatch_bf16(int bm, const GemmArgs& a, hipStream_t s) {
 // Whether a backward product runs on the persistent kernel: SwiGLU dA at any
 // width, as the recompute before it; the others at multiples of its 256-column
 // tile, and at widths that it pads by at most a third where it still gains over
-// the 256 x 128 and 256 x 64 tiles: launches of 800 tiles (three passes over the
-// CUs) or more, or, with contractions of 384 and up, passes whose tiles hold 0.65
-// of all CUs' columns in real work (0.55 against the slower 256 x 64 tiles, at
-// odd multiples of 64). Whole backward over 282 shapes, persistent against tiled:
-// from 800 tiles 1.00 to 1.62 times as fast at every width (192 to 1216); with
-// fewer, above the lines 0.97 to 1.28, below them 0.63 at the least (4 experts of
-// 600 rows). max_tiles (every expert with a ragged tile) stands for the count.
+// the 256 x 128 and 256 x 64 tiles: launches of 700 tiles (nearly three passes
+// over the CUs) or more, or, with contractions of 384 and up, passes whose tiles
+// hold 0.65 of all CUs' columns in real work (0.55 against the slower 256 x 64
+// tiles, at odd multiples of 64). Whole backward over 282 shapes, persistent
+// against tiled: from 700 tiles 1.00 to 1.62 times as fast at every width (192 to
+// 1216); with fewer, above the lines 0.97 to 1.28, below them 0.63 at the least
+// (4 experts of 600 rows).
 bool gemm_backward_pp(int bm, int epilogue, const GemmArgs& a) {
     if (bm != 256 || a.Kdim < 128) return false;
     const int cols = (a.N + 255) / 256;
     if (epilogue == EPI_DSWIGLU || a.N % 256 == 0) return true;
     if (cols * 256 * 3 > a.N * 4) return false;
-    const long long tiles = (long long)a.max_tiles * cols, passes = (tiles + 255) / 256;
-    const double fill = (double)a.max_tiles * a.N / (256.0 * 256 * passes);
-    return tiles >= 800 || (a.Kdim >= 384 && fill >= (a.N % 128 == 0 ? 0.65 : 0.55));
+    const long long tiles = (long long)a.mean_tiles * cols, passes = (tiles + 255) / 256;
+    const double fill = (double)a.mean_tiles * a.N / (256.0 * 256 * passes);
+    return tiles >= 700 || (a.Kdim >= 384 && fill >= (a.N % 128 == 0 ? 0.65 : 0.55));
 }
 
 // Backward products: the persistent kernel where gemm_backward_pp says so, N

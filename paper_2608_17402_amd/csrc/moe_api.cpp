@@ -245,14 +245,17 @@ BackwardPlan plan_backward(const moe_desc_t& d) {
     b.koff = take(((size_t)d.E + 1) * 4);
     b.gtab = take((size_t)b.ld * 4);
     b.xtab = take((size_t)b.ld * 4);
-    // Windows are cut at 128 slabs. Few experts and narrow matrices give fewer
-    // 128 x 128 tiles than the CUs hold (two each) with one item per expert: there
-    // the cut is shorter, down to 16 slabs, to spread the rows (the partial blocks
-    // stay under 512 tiles of 64 KB and one per expert). 8 experts of 8192 rows, d =
-    // h = 320: each product 98 -> 43 us, its sum 5 -> 12; of 2048 rows, 320 x 448:
-    // 40 -> 16 and 5 -> 5.
-    const int64_t tiles = (int64_t)((d.d + 127) / 128) * ((b.hh + 127) / 128), all = (int64_t)(TK / 64) + d.E;
-    b.slabs = d.E * tiles >= 512 ? kWgradSlabs : (int32_t)std::min<int64_t>(std::max<int64_t>(all * tiles / 512, 16), kWgradSlabs);
+    // Windows are cut into items of at most 128 slabs, and of fewer where the
+    // chip would otherwise wait for the longest: at most twice a CU's share of all
+    // 256 x 256 tiles (81 experts of 832 rows on average, 448 x 384, skewed, the
+    // largest with every token: each product 178 -> 76 us), and, where one item
+    // per expert gives fewer 128 x 128 tiles than the CUs hold (two each), one place's
+    // share (8 experts of 8192 rows, d = h = 320: each product 98 -> 43 us, its sum 5
+    // -> 12; of 2048 rows, 320 x 448: 40 -> 16 and 5 -> 5); never under 16.
+    auto tiles = [&](int ts) { return (int64_t)((d.d + ts - 1) / ts) * ((b.hh + ts - 1) / ts); };
+    const int64_t all = (int64_t)(TK / 64) + d.E;
+    const int64_t share = d.E * tiles(128) >= 512 ? all * tiles(256) * 2 / 256 : all * tiles(128) / 512;
+    b.slabs = (int32_t)std::min<int64_t>(std::max<int64_t>(share, 16), kWgradSlabs);
     b.items_max = d.E + (int32_t)(((size_t)b.ld / 64 + b.slabs - 1) / b.slabs);
     b.items = take((size_t)b.items_max * sizeof(WgradItem));
     b.rlist = take((size_t)d.E * sizeof(TileDesc));
@@ -454,6 +457,7 @@ static moe_status_t enqueue_backward(const moe_desc_t& d, const BackwardPlan& b,
     g.a_bytes = (uint32_t)((size_t)d.T * d.d * 2);
     g.act_n = d.h;
     g.act_ld = hh;
+    g.mean_tiles = (int32_t)((TK + 128 * (size_t)d.E + 255) / 256);
     HIP_CHECK(launch_gemm(d, sw ? EPI_SWIGLU_BWD : EPI_GELU_BWD, p.tile_bm, g, s), "backward fc1");
 
     GemmArgs ga = g;  // dH from Gout W2 and the pre-activations

@@ -87,6 +87,7 @@ struct GemmArgs {
     const void* aux;           // EPI_DGELU: the pre-activation (fp32, rows of N); EPI_DSWIGLU: G, U
     int32_t ldc;               // persistent kernel, EPI_DSWIGLU: the real column count when N
                                // is rounded up to the tile width (0 = N); columns past it are not stored
+    int32_t mean_tiles;        // backward: expected M-tiles of 256 rows (half a ragged one per expert)
     int32_t b_half;            // K-major weights of two stacked matrices: K columns of each half (act_n of them
                                // with a weight row); 0 = one matrix
     int32_t act_n;             // EPI_SWIGLU_STORE: activation width h (valid columns)
