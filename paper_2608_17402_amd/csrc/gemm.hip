@@ -2084,13 +2084,17 @@ hipError_t dispatch(const moe_desc_t& d, int epilogue, int bm, const GemmArgs& a
 
 }  // namespace
 
-// Share of a 256-CU part's time that the persistent kernel's 256 x 256 tiles
-// would spend on real rows and columns of the two grouped layers, for loads
-// known by their mean alone. A pass over the CUs costs its slabs and about nine
-// more (pipeline fill and epilogue), whether every CU has a tile or not. The
-// tiles: half a ragged tile per expert and a standard deviation of it, or, for
-// loads close to the mean, those of experts with Poisson counts.
-static double fill256(const moe_desc_t& d) {
+// What the persistent kernel's 256 x 256 tiles would do for the two grouped
+// layers on 256 CUs, for loads known by their mean alone: `share`, the part of
+// the time spent on real rows and columns, where a pass over the CUs costs its
+// slabs and about nine more (pipeline fill and epilogue) whether every CU has a
+// tile or not, and `tiles` of the narrower layer. M-tiles: half a ragged tile per
+// expert and a standard deviation of it, or, for loads close to the mean, those
+// of experts with Poisson counts.
+struct Fill256 {
+    double share, tiles;
+};
+static Fill256 fill256(const moe_desc_t& d) {
     constexpr int kCus = 256, kTail = 9;
     const bool swiglu = d.flags & MOE_FLAG_SWIGLU;
     const int hh = act_stride(d, d.h);
@@ -2104,26 +2108,44 @@ static double fill256(const moe_desc_t& d) {
     };
     layer(swiglu ? 2 * hh : hh, swiglu ? (hh + 127) / 128 : (hh + 255) / 256, d.d);
     layer(d.d, (d.d + 255) / 256, hh);
-    return work / time;
+    return {work / time, tiles * ((std::min(d.d, hh) + 255) / 256)};
+}
+
+// The least share with which the 256-row tiles are taken, by what else makes
+// them slower than 64-row tiles: few tiles (a pass that some XCD or expert
+// overfills weighs more), narrow layers (short contractions beside the
+// epilogue) and the backward's longer epilogues. Each line lies where, of 1800
+// forward pairs and 1630 backward calls of 4 to 256 experts, 128 to 511 rows,
+// widths 256 to 1536, balanced and skewed, none (backward: next to none) above it
+// was slower than with 64-row tiles: forward 0.99 to 1.50 times as fast above the
+// lines (1.07 over all shapes, 1.09 with the better of the two everywhere) and
+// 0.73 at the least below them, backward 0.94 to 1.24 (1.03 over all) and 0.70.
+static double least_share(double tiles, int width, bool swiglu, bool backward) {
+    if (backward) {
+        if (tiles >= 640) return width >= 700 ? (swiglu ? 0.28 : 0.25) : (swiglu ? 0.30 : 0.26);
+        return tiles >= 400 ? 0.295 : (tiles >= 200 ? 0.32 : 1.0);
+    }
+    if (tiles >= 640) return width >= 700 ? 0.18 : (width >= 512 ? 0.28 : 0.31);
+    if (tiles >= 400) return width >= 700 ? 0.26 : (width >= 512 ? 0.29 : 0.31);
+    return tiles >= 200 ? (swiglu && width >= 700 ? 0.28 : 0.30) : 0.32;
 }
 
 int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows, bool backward) {
     if (d.dtype != MOE_BF16) return 64;
     if (avg_rows >= 512) return 256;
+    const bool swiglu = d.flags & MOE_FLAG_SWIGLU;
+    const int hh = act_stride(d, d.h), width = hh < d.d ? hh : d.d;
     // With fewer rows the 256-row tiles (widths the persistent kernel takes, from
     // 128 rows) only where they fill enough of the chip, whatever the loads: a
     // few experts or narrow layers leave most CUs without a tile, and ragged or
     // skewed loads pad (8 experts, d = h = 768, 130 rows: 64-row tiles 17 us for
     // the two products, 256-row tiles 46; 128 experts, d = h = 512, 130 rows,
-    // skewed: 54 and 76). Over 1100 shapes of 4 to 200 experts, 128 to 511 rows,
-    // widths 256 to 1536, balanced and skewed, no forward pair lost against
-    // 64-row tiles where the fill is 0.30 or more (1.00 to 1.50 times as fast; at
-    // 0.28, 0.76 at the least), no backward from 0.34 (its products have the
-    // longer epilogues). ViT-H, 260 rows (0.32): 166 and 155 us a layer; ViT-L,
-    // 448 rows (0.35): 335 and 311; ViT-G, 160 rows (0.32): 609 and 556.
-    const int hh = act_stride(d, d.h), width = hh < d.d ? hh : d.d;
-    const bool pp = d.d % 128 == 0 && ((d.flags & MOE_FLAG_SWIGLU) || d.h % 128 == 0);
-    if (pp && avg_rows >= 128 && fill256(d) >= (backward ? 0.35 : 0.31)) return 256;
+    // skewed: 54 and 76). ViT-H, 260 rows (share 0.32): 166 and 155 us a layer;
+    // ViT-L, 448 rows (0.35): 335 and 311; ViT-G, 160 rows (0.32): 609 and 556.
+    if (d.d % 128 == 0 && (swiglu || d.h % 128 == 0) && avg_rows >= 128) {
+        const Fill256 f = fill256(d);
+        if (f.share >= least_share(f.tiles, width, swiglu, backward)) return 256;
+    }
     // 128-row tiles from 192 rows where those fill the CUs' two places about
     // twice (896 tiles in the narrower layer) and no layer is only 256 columns
     // wide (200 experts, d = h = 256, 330 rows: 64-row tiles 55 us, 128-row tiles

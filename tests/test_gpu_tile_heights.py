@@ -26,8 +26,8 @@ FORWARD = {
     "h256_500rows": (6000, 512, 48, 4, 512, "gelu"),
     "h256_rounded_640": (4000, 640, 32, 4, 640, "gelu"),
     "h256_180rows": (2160, 1024, 48, 4, 1024, "gelu"),
-    "h256_sw_180rows": (1440, 1280, 32, 4, 710, "swiglu"),
-    "h256_sw_250rows": (2000, 1280, 32, 4, 500, "swiglu"),
+    "h256_sw_180rows": (2880, 1280, 64, 4, 710, "swiglu"),
+    "h256_sw_250rows": (3500, 1024, 56, 4, 640, "swiglu"),
     "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
     "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
     "h128_sw_d576": (7200, 576, 128, 4, 500, "swiglu"),
@@ -38,7 +38,7 @@ FORWARD = {
 BACKWARD = {
     "h256_640": (4000, 768, 32, 4, 640, "gelu"),
     "h256_250rows": (2000, 1280, 32, 4, 1024, "gelu"),
-    "h256_sw": (1440, 1536, 32, 4, 710, "swiglu"),
+    "h256_sw": (2880, 1536, 64, 4, 710, "swiglu"),
     "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
     "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
     "h128_sw": (7200, 512, 128, 4, 500, "swiglu"),
