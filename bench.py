@@ -40,28 +40,29 @@ PEAK_HBM_GBS = 8000.0
 # commands and raw figures. The figures hold for the GEMM sources whose hash is
 # TRAFFIC_SOURCE_HASH: once those change, traffic is reported as null until
 # the counters are taken again.
-TRAFFIC_SOURCE_HASH = "35d87b3f8476f9ac"
-TRAFFIC_BYTES = {"vitg_skew_bf16": 6924223038, "vitl_bf16": 3643498711, "vitb_bf16": 779626301,
-                 "single_image_bf16": 1275359648, "vith_swiglu_bf16": 6605361156,
-                 "single_image_swiglu_bf16": 1879607968}
+TRAFFIC_SOURCE_HASH = "74f24a1df3874509"
+TRAFFIC_BYTES = {"vitg_skew_bf16": 6874235049, "vitl_bf16": 3642636856, "vitb_bf16": 779222449,
+                 "single_image_bf16": 1275358480, "vith_swiglu_bf16": 6528120606,
+                 "single_image_swiglu_bf16": 1879492164}
 
 
 # Every source that changes the GEMM pair's HBM bytes: the kernels, the tile
 # size choice and workspace plan, the tile table, and the workloads (the
 # skewed layer's stored bias decides its expert loads).
-TRAFFIC_SOURCES = ("paper_2608_17402_amd/csrc/gemm.hip", "paper_2608_17402_amd/csrc/moe_internal.h",
-                   "paper_2608_17402_amd/csrc/moe_api.cpp", "paper_2608_17402_amd/csrc/permute.hip",
-                   "workloads/configs.py", "workloads/generate.py", "tests/golden/vitg_skew_bias_seed0.txt")
+TRAFFIC_SOURCES = ("paper_2608_17402_amd/csrc/gemm.hip", "paper_2608_17402_amd/csrc/gemm_device.h",
+                   "paper_2608_17402_amd/csrc/moe_internal.h", "paper_2608_17402_amd/csrc/moe_api.cpp",
+                   "paper_2608_17402_amd/csrc/permute.hip", "workloads/configs.py", "workloads/generate.py",
+                   "tests/golden/vitg_skew_bias_seed0.txt")
 
 
 # HBM bytes of one expert-MLP backward call (all its kernels), from the same
 # two counters and scale factors, taken with `bench.py --mode backward`; they
 # hold for the sources whose hash is BACKWARD_TRAFFIC_SOURCE_HASH (those of
-# the forward pair and backward.hip).
-BACKWARD_TRAFFIC_SOURCE_HASH = "10192b99fe832cc7"
-BACKWARD_TRAFFIC_BYTES = {"vitg_skew_bf16": 41177098056, "vith_swiglu_bf16": 47912615423}
+# the forward pair, backward.hip and wgrad.hip).
+BACKWARD_TRAFFIC_SOURCE_HASH = "6b49ea343acfdf73"
+BACKWARD_TRAFFIC_BYTES = {"vitg_skew_bf16": 31100752913, "vith_swiglu_bf16": 38045343422}
 BACKWARD_TRAFFIC_SOURCES = TRAFFIC_SOURCES + ("paper_2608_17402_amd/csrc/backward.hip",
-                                                      "paper_2608_17402_amd/csrc/wgrad.hip")
+                                              "paper_2608_17402_amd/csrc/wgrad.hip")
 
 
 def source_hash(files):

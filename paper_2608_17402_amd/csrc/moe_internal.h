@@ -135,7 +135,7 @@ struct BackwardPlan {
     size_t partials;         // [items_max, d, hw] fp32 partial sums of split experts
     int32_t hh, hw;
     int32_t ld;              // bound on the window positions: T*K + 128 E, rounded up to 64
-    int32_t slabs;           // longest work item, in 64-row slabs (4 .. kWgradSlabs)
+    int32_t slabs;           // longest work item, in 64-row slabs (16 .. kWgradSlabs)
     int32_t items_max;       // bound on the work items (and on the partial blocks)
     size_t total;
 };
@@ -188,7 +188,7 @@ hipError_t launch_gemm(const moe_desc_t& d, int epilogue, int bm, const GemmArgs
 // Whether launch_gemm(EPI_COMBINE) supports this dense GEMM (M-tile bm, N columns, K = kdim).
 bool gemm_combine_fusable(const moe_desc_t& d, int bm, int n, int kdim);
 // Backward data movement (backward.hip).
-// Longest K window of one weight-gradient work item, in 64-column slabs.
+// Longest K window of one weight-gradient work item, in 64-row slabs.
 constexpr int kWgradSlabs = 128;
 // One work item of the weight-gradient products: klen window positions from
 // q0 (multiples of 64, at least two slabs) of expert e, whose rows are the sorted rows
