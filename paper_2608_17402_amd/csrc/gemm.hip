@@ -2127,7 +2127,8 @@ static double least_share(double tiles, int width, bool swiglu, bool backward) {
     }
     if (tiles >= 640) return width >= 700 ? 0.18 : (width >= 512 ? 0.28 : 0.31);
     if (tiles >= 400) return width >= 700 ? 0.26 : (width >= 512 ? 0.29 : 0.31);
-    return tiles >= 200 ? (swiglu && width >= 700 ? 0.28 : 0.30) : 0.32;
+    if (tiles >= 200 && swiglu && width >= 700) return 0.28;
+    return tiles >= 170 ? 0.30 : 0.32;
 }
 
 int gemm_tile_bm(const moe_desc_t& d, int64_t avg_rows, bool backward) {

@@ -28,6 +28,7 @@ FORWARD = {
     "h256_180rows": (2160, 1024, 48, 4, 1024, "gelu"),
     "h256_sw_180rows": (2880, 1280, 64, 4, 710, "swiglu"),
     "h256_sw_250rows": (3500, 1024, 56, 4, 640, "swiglu"),
+    "h256_sw_248rows": (1100, 1280, 31, 7, 854, "swiglu"),
     "h128_224rows": (7168, 512, 128, 4, 512, "gelu"),
     "h128_64cols": (7200, 576, 128, 4, 576, "gelu"),
     "h128_sw_d576": (7200, 576, 128, 4, 500, "swiglu"),
