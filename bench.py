@@ -40,10 +40,10 @@ PEAK_HBM_GBS = 8000.0
 # commands and raw figures. The figures hold for the GEMM sources whose hash is
 # TRAFFIC_SOURCE_HASH: once those change, traffic is reported as null until
 # the counters are taken again.
-TRAFFIC_SOURCE_HASH = "74f24a1df3874509"
-TRAFFIC_BYTES = {"vitg_skew_bf16": 6874235049, "vitl_bf16": 3642636856, "vitb_bf16": 779222449,
-                 "single_image_bf16": 1275358480, "vith_swiglu_bf16": 6528120606,
-                 "single_image_swiglu_bf16": 1879492164}
+TRAFFIC_SOURCE_HASH = "f2710b13a44fecbd"
+TRAFFIC_BYTES = {"vitg_skew_bf16": 6919121401, "vitl_bf16": 3644069456, "vitb_bf16": 780271789,
+                 "single_image_bf16": 1275358134, "vith_swiglu_bf16": 6565392854,
+                 "single_image_swiglu_bf16": 1879490333}
 
 
 # Every source that changes the GEMM pair's HBM bytes: the kernels, the tile
@@ -59,8 +59,8 @@ TRAFFIC_SOURCES = ("paper_2608_17402_amd/csrc/gemm.hip", "paper_2608_17402_amd/c
 # two counters and scale factors, taken with `bench.py --mode backward`; they
 # hold for the sources whose hash is BACKWARD_TRAFFIC_SOURCE_HASH (those of
 # the forward pair, backward.hip and wgrad.hip).
-BACKWARD_TRAFFIC_SOURCE_HASH = "6b49ea343acfdf73"
-BACKWARD_TRAFFIC_BYTES = {"vitg_skew_bf16": 31100752913, "vith_swiglu_bf16": 38045343422}
+BACKWARD_TRAFFIC_SOURCE_HASH = "22c22a57ff49a5cb"
+BACKWARD_TRAFFIC_BYTES = {"vitg_skew_bf16": 31239784318, "vith_swiglu_bf16": 38179689080}
 BACKWARD_TRAFFIC_SOURCES = TRAFFIC_SOURCES + ("paper_2608_17402_amd/csrc/backward.hip",
                                               "paper_2608_17402_amd/csrc/wgrad.hip")
 
